@@ -60,7 +60,8 @@ unsigned blocks_per_cu_lds(int blocks);
 
 // grad_dtype: PS_F32 | PS_BF16. pull_dtype: -1 (no replicas), PS_F32, PS_BF16.
 // level: 2 = every buffer 16-byte aligned; 1 = fp32 buffers 16-byte and bf16
-// buffers 8-byte aligned; 0 = anything else (scalar kernels).
+// buffers 8-byte aligned; 0 = anything else (scalar kernels). The pull has two:
+// 1 = every replica on a boundary of its elements, 0 = scalar.
 // shape: residency and group size of the vector kernels (the scalar kernel
 // for misaligned buffers ignores it).
 hipError_t launch_apply(const ApplyArgs &a, int grad_dtype, int pull_dtype, int level,

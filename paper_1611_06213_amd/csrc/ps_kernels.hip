@@ -116,6 +116,11 @@ constexpr uint64_t kMaxBlocks = 0xffffffffull / kBlock;
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+// The same from any element boundary: gfx950 loads and stores 16 bytes from
+// any address in one instruction.
+typedef f32x4 f32x4_any __attribute__((aligned(4)));
+typedef u32x2 u32x2_any __attribute__((aligned(2)));
+typedef u32x4 u32x4_any __attribute__((aligned(2)));
 
 // ---------------------------------------------------------------- loads
 
@@ -128,7 +133,7 @@ __device__ __forceinline__ void ld_f32(float (&x)[E], const float *p) {
     } else {
 #pragma unroll
         for (int h = 0; h < E / 4; ++h) {
-            const f32x4 *q = reinterpret_cast<const f32x4 *>(p) + h;
+            const f32x4_any *q = reinterpret_cast<const f32x4_any *>(p + 4 * h);
             f32x4 t = NT ? __builtin_nontemporal_load(q) : *q;
             x[4 * h] = t.x; x[4 * h + 1] = t.y; x[4 * h + 2] = t.z; x[4 * h + 3] = t.w;
         }
@@ -143,7 +148,7 @@ __device__ __forceinline__ void st_f32(float *p, const float (&x)[E]) {
 #pragma unroll
         for (int h = 0; h < E / 4; ++h) {
             f32x4 t = {x[4 * h], x[4 * h + 1], x[4 * h + 2], x[4 * h + 3]};
-            f32x4 *q = reinterpret_cast<f32x4 *>(p) + h;
+            f32x4_any *q = reinterpret_cast<f32x4_any *>(p + 4 * h);
             if constexpr (NT) __builtin_nontemporal_store(t, q); else *q = t;
         }
     }
@@ -234,13 +239,13 @@ __device__ __forceinline__ uint32_t bf16x2_rne(float a, float b) {
 // One replica's values for coordinates i .. i+E-1 (i a multiple of E).
 // Replicas are not read back by the server, so the stores carry the
 // non-temporal hint.
-template <int PDT, int E>
+template <int PDT, int E, bool NT = true>
 __device__ __forceinline__ void st_dst(void *d, uint64_t i, const float (&x)[E]) {
     if constexpr (PDT == PS_F32) {
         if constexpr (E == 1) {
             static_cast<float *>(d)[i] = x[0];
         } else {
-            st_f32<E, true>(static_cast<float *>(d) + i, x);
+            st_f32<E, NT>(static_cast<float *>(d) + i, x);
         }
     } else {
         if constexpr (E == 8) {
@@ -249,12 +254,14 @@ __device__ __forceinline__ void st_dst(void *d, uint64_t i, const float (&x)[E])
             t.y = bf16x2_rne(x[2], x[3]);
             t.z = bf16x2_rne(x[4], x[5]);
             t.w = bf16x2_rne(x[6], x[7]);
-            __builtin_nontemporal_store(t, reinterpret_cast<u32x4 *>(d) + (i >> 3));
+            u32x4_any *q = reinterpret_cast<u32x4_any *>(static_cast<uint16_t *>(d) + i);
+            if constexpr (NT) __builtin_nontemporal_store(t, q); else *q = t;
         } else if constexpr (E == 4) {
             u32x2 t;
             t.x = bf16x2_rne(x[0], x[1]);
             t.y = bf16x2_rne(x[2], x[3]);
-            __builtin_nontemporal_store(t, reinterpret_cast<u32x2 *>(d) + (i >> 2));
+            u32x2_any *q = reinterpret_cast<u32x2_any *>(static_cast<uint16_t *>(d) + i);
+            if constexpr (NT) __builtin_nontemporal_store(t, q); else *q = t;
         } else {
             static_cast<uint16_t *>(d)[i] = static_cast<uint16_t>(bf16x2_rne(x[0], 0.0f));
         }
@@ -449,22 +456,53 @@ __global__ void __launch_bounds__(kBlock) apply_scalar(const A a) {
 
 // ---------------------------------------------------------------- pull
 
-template <int PDT, int E, bool NT, class P>
-__device__ __forceinline__ void pull_chunk(const P &a, uint64_t i) {
-    float w[E];
-    ld_f32<E, NT>(w, a.w + i);
-    for (int r = 0; r < a.r; ++r) st_dst<PDT, E>(a.dst[r], i, w);
+// Coordinates of replica d before its first 128-byte line boundary (at most
+// n). With HEAD the fan-outs cut a replica into chunks from that boundary on,
+// so that every vector store is aligned and every line but the first and last
+// is written whole by one block, wherever the buffer starts (a row of a packed
+// tensor as well as an allocation); the loads of w, which is re-read from
+// cache, take the odd address instead. 100M coordinates, 16 replicas at odd
+// fp32 offsets 1.39 ms (one coordinate per lane 2.12), at 16-byte ones 1.39
+// (chunks from the replica's start 1.49); bf16 at odd offsets 0.86 (1.39).
+// Without it (every replica on a line boundary) the head is 0 and known before
+// the replica's address is: waiting for that cost VGG-16's fan-out 8%.
+template <int PDT, bool HEAD>
+__device__ __forceinline__ uint64_t head_of(const void *d, uint64_t n) {
+    if constexpr (!HEAD) return 0;
+    constexpr unsigned es = PDT == PS_F32 ? 4 : 2;
+    const uint64_t h = (0u - static_cast<unsigned>(reinterpret_cast<uintptr_t>(d)) & 127u) / es;
+    return h < n ? h : n;
 }
 
-// One pass: each lane reads its chunk of w once and writes it to every
-// replica. Used for a single replica (a plain streaming copy).
+// The coordinates outside replica d's whole chunks, one per lane (j-th of at
+// most 63 + 7): the head before them and the tail after them.
 template <int PDT, class P>
+__device__ __forceinline__ void pull_ends(const P &a, void *d, uint64_t h, uint64_t in_chunks,
+                                          unsigned j) {
+    if (j >= a.n - in_chunks) return;
+    const uint64_t i = j < h ? j : in_chunks + j;
+    float w[1];
+    ld_f32<1, false>(w, a.w + i);
+    st_dst<PDT, 1>(d, i, w);
+}
+
+// One pass per replica: each lane reads its chunk of w and writes it. Used
+// for a single replica (a plain streaming copy).
+template <int PDT, int E, bool HEAD, class P>
 __global__ void __launch_bounds__(kBlock) pull_vec(const P a) {
-    const uint64_t chunks = a.n >> 2;
     const uint64_t tid = static_cast<uint64_t>(blockIdx.x) * kBlock + threadIdx.x;
     const uint64_t stride = static_cast<uint64_t>(gridDim.x) * kBlock;
-    for (uint64_t c = tid; c < chunks; c += stride) pull_chunk<PDT, 4, true>(a, c << 2);
-    if (tid < a.n - (chunks << 2)) pull_chunk<PDT, 1, true>(a, (chunks << 2) + tid);
+    for (int r = 0; r < a.r; ++r) {
+        void *d = a.dst[r];
+        const uint64_t h = head_of<PDT, HEAD>(d, a.n);
+        const uint64_t chunks = (a.n - h) / E;
+        for (uint64_t c = tid; c < chunks; c += stride) {
+            float w[E];
+            ld_f32<E, true>(w, a.w + h + c * E);
+            st_dst<PDT, E>(d, h + c * E, w);
+        }
+        if (blockIdx.x == 0) pull_ends<PDT>(a, d, h, chunks * E, threadIdx.x);
+    }
 }
 
 // Tiled fan-outs for R >= 2 replicas. w is cut into tiles; blocks enumerate
@@ -489,30 +527,26 @@ __global__ void __launch_bounds__(kBlock) pull_vec(const P a) {
 constexpr uint64_t kTiledCoords = uint64_t(4) << 20;
 constexpr unsigned kTileBlocks = 4096;      // most blocks per (tile, replica)
 
-template <int PDT, int E, class P>
+template <int PDT, int E, bool HEAD, class P>
 __global__ void __launch_bounds__(kBlock) pull_tiled(const P a, unsigned bpt) {
     constexpr uint64_t kTileChunksE = kTiledCoords / E;
-    const uint64_t chunks = a.n / E;
     const unsigned b0 = blockIdx.x % bpt;
     const unsigned b = (bpt & 7u) == 0 ? (b0 & 7u) * (bpt >> 3) + (b0 >> 3) : b0;
     const unsigned tr = blockIdx.x / bpt;
     const int r = static_cast<int>(tr % static_cast<unsigned>(a.r));
     const uint64_t t = tr / static_cast<unsigned>(a.r);
+    void *d = a.dst[r];
+    const uint64_t h = head_of<PDT, HEAD>(d, a.n);
+    const uint64_t chunks = (a.n - h) / E;
     const uint64_t c0 = t * kTileChunksE;
     const uint64_t c1 = c0 + kTileChunksE < chunks ? c0 + kTileChunksE : chunks;
-    void *d = a.dst[r];
     for (uint64_t c = c0 + static_cast<uint64_t>(b) * kBlock + threadIdx.x; c < c1;
          c += static_cast<uint64_t>(bpt) * kBlock) {
         float w[E];
-        ld_f32<E, false>(w, a.w + c * E);
-        st_dst<PDT, E>(d, c * E, w);
+        ld_f32<E, false>(w, a.w + h + c * E);
+        st_dst<PDT, E>(d, h + c * E, w);
     }
-    if (t == 0 && b == 0 && threadIdx.x < a.n - chunks * E) {
-        const uint64_t i = chunks * E + threadIdx.x;
-        float w[1];
-        ld_f32<1, false>(w, a.w + i);
-        st_dst<PDT, 1>(d, i, w);
-    }
+    if (t == 0 && b == 0) pull_ends<PDT>(a, d, h, chunks * E, threadIdx.x);
 }
 
 // pull_slices: the same fan-out over 2 Mi-coordinate tiles on a 3-D grid
@@ -528,13 +562,15 @@ __global__ void __launch_bounds__(kBlock) pull_tiled(const P a, unsigned bpt) {
 // 0.172 vs 0.185 ms).
 constexpr uint64_t kSliceTileCoords = uint64_t(2) << 20;
 
-template <int PDT, int E, class P>
+template <int PDT, int E, bool HEAD, class P>
 __global__ void __launch_bounds__(kBlock) pull_slices(const P a) {
     constexpr uint64_t kTileChunksE = kSliceTileCoords / E;
-    const uint64_t chunks = a.n / E;
+    void *d = a.dst[blockIdx.y];
+    const uint64_t h = head_of<PDT, HEAD>(d, a.n);
+    const uint64_t chunks = (a.n - h) / E;
     const unsigned b = blockIdx.x;
     const uint64_t t = blockIdx.z;
-    const uint64_t c0 = t * kTileChunksE;
+    const uint64_t c0 = t * kTileChunksE < chunks ? t * kTileChunksE : chunks;
     const uint64_t c1 = c0 + kTileChunksE < chunks ? c0 + kTileChunksE : chunks;
     uint64_t lo = c0, hi = c1, j = b, nj = gridDim.x;
     if ((gridDim.x & 7u) == 0) {
@@ -545,19 +581,13 @@ __global__ void __launch_bounds__(kBlock) pull_slices(const P a) {
         j = b >> 3;
         nj = gridDim.x >> 3;
     }
-    void *d = a.dst[blockIdx.y];
     const uint64_t step = nj * kBlock;
     for (uint64_t c = lo + j * kBlock + threadIdx.x; c < hi; c += step) {
         float w[E];
-        ld_f32<E, false>(w, a.w + c * E);
-        st_dst<PDT, E>(d, c * E, w);
+        ld_f32<E, false>(w, a.w + h + c * E);
+        st_dst<PDT, E>(d, h + c * E, w);
     }
-    if (t == 0 && b == 0 && threadIdx.x < a.n - chunks * E) {
-        const uint64_t i = chunks * E + threadIdx.x;
-        float w[1];
-        ld_f32<1, false>(w, a.w + i);
-        st_dst<PDT, 1>(d, i, w);
-    }
+    if (t == 0 && b == 0) pull_ends<PDT>(a, d, h, chunks * E, threadIdx.x);
 }
 
 // Scalar path for replicas without vector alignment.
@@ -565,7 +595,11 @@ template <int PDT, class P>
 __global__ void __launch_bounds__(kBlock) pull_scalar(const P a) {
     const uint64_t tid = static_cast<uint64_t>(blockIdx.x) * kBlock + threadIdx.x;
     const uint64_t stride = static_cast<uint64_t>(gridDim.x) * kBlock;
-    for (uint64_t i = tid; i < a.n; i += stride) pull_chunk<PDT, 1, false>(a, i);
+    for (uint64_t i = tid; i < a.n; i += stride) {
+        float w[1];
+        ld_f32<1, false>(w, a.w + i);
+        for (int r = 0; r < a.r; ++r) st_dst<PDT, 1>(a.dst[r], i, w);
+    }
 }
 
 __global__ void __launch_bounds__(kBlock) zero_f32(float *p, uint64_t n) {
@@ -677,25 +711,30 @@ hipError_t go_apply_g(const A &a, int gdt, int pdt, int level, const Shape &sh,
     return go_apply_p<MOM, PS_F32>(a, pdt, level, sh, geo, s);
 }
 
+ApplyArgsC compact(const ApplyArgs &a) {
+    ApplyArgsC c;
+    c.w = a.w;
+    c.v = a.v;
+    c.n = a.n;
+    c.lr = a.lr;
+    c.m = a.m;
+    c.k = a.k;
+    c.r = a.r;
+    c.fronts_log2 = a.fronts_log2;
+    for (int j = 0; j < kCompact; ++j) {
+        c.g[j] = j < a.k ? a.g[j] : nullptr;
+        c.dst[j] = j < a.r ? a.dst[j] : nullptr;
+    }
+    return c;
+}
+
 }  // namespace
 
 hipError_t launch_apply(const ApplyArgs &a, int grad_dtype, int pull_dtype, int level,
                         const Shape &shape, const Geometry &geo, hipStream_t s) {
     if (a.r == 0) pull_dtype = -1;
     if (a.k <= kCompact && a.r <= kCompact) {
-        ApplyArgsC c;
-        c.w = a.w;
-        c.v = a.v;
-        c.n = a.n;
-        c.lr = a.lr;
-        c.m = a.m;
-        c.k = a.k;
-        c.r = a.r;
-        c.fronts_log2 = a.fronts_log2;
-        for (int j = 0; j < kCompact; ++j) {
-            c.g[j] = j < a.k ? a.g[j] : nullptr;
-            c.dst[j] = j < a.r ? a.dst[j] : nullptr;
-        }
+        const ApplyArgsC c = compact(a);
         if (c.v != nullptr) return go_apply_g<true>(c, grad_dtype, pull_dtype, level, shape, geo, s);
         return go_apply_g<false>(c, grad_dtype, pull_dtype, level, shape, geo, s);
     }
@@ -703,7 +742,7 @@ hipError_t launch_apply(const ApplyArgs &a, int grad_dtype, int pull_dtype, int 
     return go_apply_g<false>(a, grad_dtype, pull_dtype, level, shape, geo, s);
 }
 
-template <int PDT, int E, class P>
+template <int PDT, int E, bool HEAD, class P>
 void go_pull_tiled(const P &a, const Geometry &geo, hipStream_t s) {
     const uint64_t chunks = a.n / E;
     const bool one_d = PDT == PS_F32 && chunks / (kTiledCoords / E) >= 8;
@@ -717,7 +756,7 @@ void go_pull_tiled(const P &a, const Geometry &geo, hipStream_t s) {
         if (bx < 1) bx = 1;
         if (bx > 8) bx = (bx + 7) / 8 * 8;
         if (tiles <= 65535 && bx * tiles * static_cast<uint64_t>(a.r) <= kMaxBlocks) {
-            hipLaunchKernelGGL((pull_slices<PDT, E, P>),
+            hipLaunchKernelGGL((pull_slices<PDT, E, HEAD, P>),
                                dim3(static_cast<unsigned>(bx), static_cast<unsigned>(a.r),
                                     static_cast<unsigned>(tiles)),
                                dim3(kBlock), 0, s, a);
@@ -735,26 +774,34 @@ void go_pull_tiled(const P &a, const Geometry &geo, hipStream_t s) {
     if (groups * bpt > kMaxBlocks) bpt = kMaxBlocks / groups;   // lanes stride further
     if (bpt < 1) {
         // more (tile, replica) pairs than a grid can hold: one pass per lane
-        hipLaunchKernelGGL((pull_vec<PDT, P>), dim3(grid_for(a.n >> 2, geo)), dim3(kBlock), 0, s,
+        hipLaunchKernelGGL((pull_vec<PDT, E, HEAD, P>), dim3(grid_for(a.n / E, geo)), dim3(kBlock), 0, s,
                            a);
         return;
     }
-    hipLaunchKernelGGL((pull_tiled<PDT, E, P>), dim3(static_cast<unsigned>(groups * bpt)),
+    hipLaunchKernelGGL((pull_tiled<PDT, E, HEAD, P>), dim3(static_cast<unsigned>(groups * bpt)),
                        dim3(kBlock), 0, s, a, static_cast<unsigned>(bpt));
+}
+
+template <int PDT, bool HEAD, class P>
+void go_pull_vec(const P &a, const Geometry &geo, hipStream_t s) {
+    constexpr int E = PDT == PS_BF16 ? 8 : 4;
+    if (a.r == 1)
+        hipLaunchKernelGGL((pull_vec<PDT, E, HEAD, P>), dim3(grid_for(a.n / E, geo)), dim3(kBlock),
+                           0, s, a);
+    else
+        go_pull_tiled<PDT, E, HEAD>(a, geo, s);
 }
 
 template <int PDT, class P>
 void go_pull(const P &a, int level, const Geometry &geo, hipStream_t s) {
     if (level == 0) {
         hipLaunchKernelGGL((pull_scalar<PDT, P>), dim3(grid_for(a.n, geo)), dim3(kBlock), 0, s, a);
-    } else if (a.r == 1) {
-        hipLaunchKernelGGL((pull_vec<PDT, P>), dim3(grid_for(a.n >> 2, geo)), dim3(kBlock), 0, s,
-                           a);
-    } else if (PDT == PS_BF16 && level == 2) {
-        go_pull_tiled<PDT, 8>(a, geo, s);
-    } else {
-        go_pull_tiled<PDT, 4>(a, geo, s);
+        return;
     }
+    bool head = false;   // some replica starts inside a 128-byte line
+    for (int r = 0; r < a.r; ++r) head = head || reinterpret_cast<uintptr_t>(a.dst[r]) % 128 != 0;
+    if (head) go_pull_vec<PDT, true>(a, geo, s);
+    else go_pull_vec<PDT, false>(a, geo, s);
 }
 
 hipError_t launch_sync(const ApplyArgs &a, int grad_dtype, int level, const Shape &shape,

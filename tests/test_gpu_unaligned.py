@@ -1,0 +1,66 @@
+"""Gradients and replicas on element boundaries: the vector kernels serve them
+from any 4-byte (gradients) and any element (replicas) boundary. Bitwise against
+the oracle, with guard values around every replica."""
+import numpy as np
+import pytest
+
+from oracle import server as orc
+from paper_1611_06213_amd import ps
+from tests import parity
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a GPU")
+    ps.load_library()
+    return torch
+
+
+PAD = 64   # values before and after each replica: 128 bytes of bf16
+
+
+@pytest.mark.parametrize("n", [1, 2, 31, 32, 33, 63, 64, 65, 127, 129, 1023, 2053, 70_001])
+def test_replicas_at_every_boundary(torch, n):
+    """Fan-outs to one and to several replicas that start at every element of a
+    128-byte line: all of each replica and nothing around it."""
+    w0 = (torch.rand(n, device="cuda") - 0.5) * 0.1
+    srv = ps.ParameterServer(n, 0.01, 0.0, queue_depth=1)
+    srv.set_pull_skip(False)
+    srv.set_weights(w0)
+    w = parity.np_bits(w0)
+    for tdt, want in ((torch.float32, w), (torch.bfloat16, orc.f32_to_bf16(w))):
+        ibits = torch.int32 if tdt == torch.float32 else torch.int16
+        want = torch.from_numpy(want.view(np.int32 if tdt == torch.float32 else np.int16)).cuda()
+        for offs in ([o] for o in range(64)) if n < 2000 else ([0], [1], [31], [63]):
+            for r in (1, 3):
+                bufs = [torch.full((n + 2 * PAD,), 7.0, dtype=tdt, device="cuda") for _ in range(r)]
+                dsts = [b[(offs[0] + j) % PAD:][:n] for j, b in enumerate(bufs)]
+                srv.pull_many(list(range(r)), dsts)
+                srv.sync()
+                for j, (b, d) in enumerate(zip(bufs, dsts)):
+                    lo = (offs[0] + j) % PAD
+                    assert torch.equal(d.view(ibits), want), (tdt, offs, r, j)
+                    assert bool((b[:lo] == 7.0).all() and (b[lo + n:] == 7.0).all()), (tdt, offs, r, j)
+    srv.close()
+
+
+@pytest.mark.parametrize("n", [8 * (4 << 20) + 77, 7 * (2 << 20) - 3])
+def test_tiled_fan_outs_at_odd_boundaries(torch, n):
+    """The 1-D and the sliced tiled fan-out, replicas 1..3 elements off."""
+    w0 = (torch.rand(n, device="cuda") - 0.5) * 0.1
+    srv = ps.ParameterServer(n, 0.01, 0.0, queue_depth=1)
+    srv.set_weights(w0)
+    w = parity.np_bits(w0)
+    for tdt, want in ((torch.float32, w), (torch.bfloat16, orc.f32_to_bf16(w))):
+        ibits = torch.int32 if tdt == torch.float32 else torch.int16
+        want = torch.from_numpy(want.view(np.int32 if tdt == torch.float32 else np.int16)).cuda()
+        dsts = list(torch.full((3, n), float("nan"), dtype=tdt, device="cuda"))
+        srv.pull_many([0, 1, 2], dsts)
+        srv.sync()
+        for j, d in enumerate(dsts):
+            assert torch.equal(d.view(ibits), want), (tdt, j)
+    srv.close()
