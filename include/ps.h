@@ -194,6 +194,8 @@ int ps_apply_pull(ps_server *ps, int n, const int *learner_ids, void *const *dst
  * always, up to 4 when the apply folds at most 16 gradients, up to 6 when it
  * folds at most 8 into a vector of fewer than 20M coordinates (measured
  * faster there; with more gradients or replicas the separate fan-out is).
+ * In a script (ps_run, graphs) a limit of 0 or more holds for every pull that
+ * would otherwise be written together with the applies around it.
  * Results are identical either way. PS_EINVAL for other values. */
 int ps_set_pull_fusion(ps_server *ps, int max_replicas);
 
@@ -399,6 +401,11 @@ typedef struct ps_op {
  * schedule without a host-language round trip per call. Stops at the first
  * call that does not return PS_OK (a full queue included) and returns its
  * status; *done (may be NULL) receives the number of calls completed.
+ * Consecutive applies and the pulls between them may go out as one kernel
+ * launch (up to PS_MAX_QUEUE_DEPTH gradients and PS_MAX_REPLICAS replicas),
+ * with the same results; every kernel has been enqueued when ps_run returns.
+ * If such a launch fails (PS_EHIP), *done counts the calls before the ones
+ * that went out in it.
  * PS_EINVAL for an unknown kind or ops == NULL with count > 0. */
 int ps_run(ps_server *ps, const ps_op *ops, int count, int *done);
 

@@ -25,6 +25,15 @@ struct ApplyArgs {
     void *dst[PS_MAX_REPLICAS];
 };
 
+// Several steps in one pass: gradients 0..k-1 in order, and after gradient j
+// the replicas dst[e(j-1)] .. dst[e(j)-1], where e(j) is byte j of rend (byte
+// j % 8, least significant first, of word j / 8; not decreasing, and r for the
+// last gradient).
+struct StepsArgs : ApplyArgs {
+    uint64_t rend[PS_MAX_QUEUE_DEPTH / 8];
+    uint64_t again;   // bit r: dst[r] is the buffer of a later replica too
+};
+
 struct PullArgs {
     const float *w;
     uint64_t n;
@@ -66,6 +75,9 @@ unsigned blocks_per_cu_lds(int blocks);
 // for misaligned buffers ignores it).
 hipError_t launch_apply(const ApplyArgs &a, int grad_dtype, int pull_dtype, int level,
                         const Shape &shape, const Geometry &geo, hipStream_t s);
+// Steps in one launch; every buffer on a boundary the vector kernels take.
+hipError_t launch_steps(const StepsArgs &a, int grad_dtype, int pull_dtype, int blocks_per_cu,
+                        const Geometry &geo, hipStream_t s);
 hipError_t launch_pull(const PullArgs &a, int pull_dtype, int level, const Geometry &geo,
                        hipStream_t s);
 // Synchronous step over a.k gradients of one dtype (no replicas).

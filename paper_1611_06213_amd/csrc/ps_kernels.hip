@@ -78,6 +78,10 @@ struct ApplyArgsC {
     const void *g[kCompact];
     void *dst[kCompact];
 };
+struct StepsArgsC : ApplyArgsC {
+    uint64_t rend[kCompact / 8];
+    uint64_t again;
+};
 struct PullArgsC {
     const float *w;
     uint64_t n;
@@ -446,6 +450,96 @@ __global__ void __launch_bounds__(kBlock) apply_vec(const A a) {
     if (tid < a.n - chunks * E) apply_chunk<MOM, GDT, PDT, 1, G>(a, chunks * E + tid);
 }
 
+// ---------------------------------------------------------------- steps
+
+// The kernel arguments where they lie, in constant memory: the steps kernel
+// indexes them with loop counters, for which the compiler would otherwise
+// copy a by-value argument block to scratch.
+template <class A>
+using KernArgs = const A __attribute__((address_space(4))) *;
+
+// Gradients k0 .. k0+G-1 of a run of steps (G at most 8, or 16), each
+// followed by the replicas pulled after it: as apply_group, with the stores
+// of dst[r] .. between the updates. A replica that a later step of this
+// launch writes again is stored with the ordinary policy, so that its line is
+// still in L2 then and reaches HBM once (16 steps of 4 gradients and the same
+// 4 replicas, 4M coordinates: 243 us, 361 with the non-temporal hint); the
+// last write of each carries the hint (all plain: up to 5% slower where
+// every step writes other replicas).
+template <bool MOM, int GDT, int PDT, int E, int G, class A>
+__device__ __forceinline__ void steps_group(KernArgs<A> a, int k0, uint64_t i, float (&w)[E],
+                                            float (&v)[E], float lr, float m, int &r) {
+    GradBits<GDT, E> b[G];
+#pragma unroll
+    for (int j = 0; j < G; ++j) b[j] = ld_bits<GDT, E>(a->g[k0 + j], i);
+    uint64_t ends[(G + 7) / 8];
+#pragma unroll
+    for (int h = 0; h < (G + 7) / 8; ++h) ends[h] = a->rend[(k0 >> 3) + h];
+    const uint64_t again = a->again;
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < G; ++j) {
+        float g[E];
+        widen<GDT, E>(g, b[j]);
+        step<MOM, E>(w, v, g, lr, m);
+        const int end = static_cast<int>(ends[j >> 3] >> (8 * (j & 7))) & 255;
+        for (; r < end; ++r) {
+            if ((again >> r) & 1) {
+                st_dst<PDT, E, false>(a->dst[r], i, w);
+                asm volatile("");   // or the compiler makes the two stores one, without the hint
+            } else {
+                st_dst<PDT, E>(a->dst[r], i, w);
+            }
+        }
+    }
+}
+
+template <bool MOM, int GDT, int PDT, int E, class A>
+__device__ __forceinline__ void steps_chunk(KernArgs<A> a, uint64_t i) {
+    // 16 gradients' loads at once (8: 0-8% slower; 24: within 1%)
+    constexpr int G = sizeof(A::rend) == 8 ? 8 : 16;
+    float w[E], v[E];
+    ld_f32<E, nt_wv_ld<E>()>(w, a->w + i);
+    if constexpr (MOM) ld_f32<E, nt_wv_ld<E>()>(v, a->v + i);
+    const float lr = a->lr;
+    const float m = a->m;
+    const int k = a->k;
+    int r = 0, k0 = 0;
+    if (k >= G) {
+        steps_group<MOM, GDT, PDT, E, G, A>(a, 0, i, w, v, lr, m, r);
+        k0 = G;
+    }
+    for (; k0 + G <= k; k0 += G) steps_group<MOM, GDT, PDT, E, G, A>(a, k0, i, w, v, lr, m, r);
+    if constexpr (G > 8) {
+        if (k0 + 8 <= k) {
+            steps_group<MOM, GDT, PDT, E, 8, A>(a, k0, i, w, v, lr, m, r);
+            k0 += 8;
+        }
+    }
+    switch (k - k0) {
+        case 1: steps_group<MOM, GDT, PDT, E, 1, A>(a, k0, i, w, v, lr, m, r); break;
+        case 2: steps_group<MOM, GDT, PDT, E, 2, A>(a, k0, i, w, v, lr, m, r); break;
+        case 3: steps_group<MOM, GDT, PDT, E, 3, A>(a, k0, i, w, v, lr, m, r); break;
+        case 4: steps_group<MOM, GDT, PDT, E, 4, A>(a, k0, i, w, v, lr, m, r); break;
+        case 5: steps_group<MOM, GDT, PDT, E, 5, A>(a, k0, i, w, v, lr, m, r); break;
+        case 6: steps_group<MOM, GDT, PDT, E, 6, A>(a, k0, i, w, v, lr, m, r); break;
+        case 7: steps_group<MOM, GDT, PDT, E, 7, A>(a, k0, i, w, v, lr, m, r); break;
+        default: break;
+    }
+    st_f32<E, nt_wv_st<E>()>(a->w + i, w);
+    if constexpr (MOM) st_f32<E, nt_wv_st<E>()>(a->v + i, v);
+}
+
+template <bool MOM, int GDT, int PDT, int E, class A>
+__global__ void __launch_bounds__(kBlock) apply_vec_steps(const A) {
+    const KernArgs<A> a = (KernArgs<A>)__builtin_amdgcn_kernarg_segment_ptr();
+    const uint64_t chunks = a->n / E;
+    const uint64_t tid = static_cast<uint64_t>(blockIdx.x) * kBlock + threadIdx.x;
+    const uint64_t stride = static_cast<uint64_t>(gridDim.x) * kBlock;
+    for (uint64_t c = tid; c < chunks; c += stride) steps_chunk<MOM, GDT, PDT, E, A>(a, c * E);
+    if (tid < a->n - chunks * E) steps_chunk<MOM, GDT, PDT, 1, A>(a, chunks * E + tid);
+}
+
 // Scalar path for buffers without vector alignment: one coordinate per lane.
 template <bool MOM, int GDT, int PDT, class A>
 __global__ void __launch_bounds__(kBlock) apply_scalar(const A a) {
@@ -740,6 +834,42 @@ hipError_t launch_apply(const ApplyArgs &a, int grad_dtype, int pull_dtype, int 
     }
     if (a.v != nullptr) return go_apply_g<true>(a, grad_dtype, pull_dtype, level, shape, geo, s);
     return go_apply_g<false>(a, grad_dtype, pull_dtype, level, shape, geo, s);
+}
+
+template <bool MOM, class A>
+hipError_t go_steps(const A &a, int gdt, int pdt, unsigned lds, const Geometry &geo,
+                    hipStream_t s) {
+    const dim3 block(kBlock);
+    if (gdt == PS_F32) {
+        const dim3 grid(grid_for(a.n / 4, geo));
+        if (pdt == PS_F32)
+            hipLaunchKernelGGL((apply_vec_steps<MOM, PS_F32, PS_F32, 4, A>), grid, block, lds, s, a);
+        else
+            hipLaunchKernelGGL((apply_vec_steps<MOM, PS_F32, PS_BF16, 4, A>), grid, block, lds, s, a);
+    } else {
+        const dim3 grid(grid_for(a.n / 8, geo));
+        if (pdt == PS_F32)
+            hipLaunchKernelGGL((apply_vec_steps<MOM, PS_BF16, PS_F32, 8, A>), grid, block, lds, s, a);
+        else
+            hipLaunchKernelGGL((apply_vec_steps<MOM, PS_BF16, PS_BF16, 8, A>), grid, block, lds, s, a);
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_steps(const StepsArgs &a, int grad_dtype, int pull_dtype, int blocks_per_cu,
+                        const Geometry &geo, hipStream_t s) {
+    const unsigned lds =
+        (blocks_per_cu >= 1 && blocks_per_cu <= 4) ? geo.lds_for_blocks[blocks_per_cu] : 0;
+    if (a.k <= kCompact && a.r <= kCompact) {
+        StepsArgsC c;
+        static_cast<ApplyArgsC &>(c) = compact(a);
+        c.rend[0] = a.rend[0];
+        c.again = a.again;
+        return c.v != nullptr ? go_steps<true>(c, grad_dtype, pull_dtype, lds, geo, s)
+                              : go_steps<false>(c, grad_dtype, pull_dtype, lds, geo, s);
+    }
+    return a.v != nullptr ? go_steps<true>(a, grad_dtype, pull_dtype, lds, geo, s)
+                          : go_steps<false>(a, grad_dtype, pull_dtype, lds, geo, s);
 }
 
 template <int PDT, int E, bool HEAD, class P>

@@ -114,6 +114,10 @@ ApplyShape sync_shape(int k, bool momentum, bool bf16) {
     return {1, 0, 16};
 }
 
+int steps_blocks_per_cu(size_t bytes, size_t n) {
+    return bytes <= 8 || (bytes <= 16 && n < 8000000) ? 2 : 1;
+}
+
 bool fuse_replicas(int r, int k, size_t n) {
     return r <= 1 || (r <= 4 && k <= 16) || (r <= 6 && k <= 8 && n < kSmallVector);
 }

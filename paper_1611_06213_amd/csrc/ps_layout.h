@@ -89,6 +89,16 @@ ApplyShape apply_shape(int k, bool momentum, bool bf16, size_t n);
 // fronts choice beyond the phase rule: fronts_log2 is 0).
 ApplyShape sync_shape(int k, bool momentum, bool bf16);
 
+// Resident blocks per compute unit of a launch of several steps (launch_steps)
+// whose steps write `bytes` replica bytes per coordinate each: two while they
+// write little, one beyond (more waves then keep more half-written lines of
+// more replicas in cache than it holds). From server rows with momentum, two
+// against one: 60M coordinates, 2 gradients and 4 bf16 replicas a step 573 vs
+// 696 us (4 steps), 1 and 1 fp32 479 vs 502 us; 2 and 4 fp32 957 vs 936, 8 and
+// 8 fp32 2062 vs 1916; 4M, 2 and 4 fp32 202 vs 207 us (16 steps), 8 and 8 fp32
+// 506 vs 455; 1M, 1 and 16 fp32 79.8 vs 71.0 us (8 steps).
+int steps_blocks_per_cu(size_t bytes, size_t n);
+
 // Whether ps_apply_pull writes its r replicas from the apply pass over k
 // gradients of an n-coordinate vector (else the apply is followed by the
 // tiled fan-out): one replica always; up to 4 when at most 16 gradients are
