@@ -114,6 +114,14 @@ ApplyShape sync_shape(int k, bool momentum, bool bf16) {
     return {1, 0, 16};
 }
 
+bool steps_join(size_t grad_bytes, size_t pull_bytes, bool momentum, size_t n) {
+    const size_t saved = (momentum ? 16 : 8) + 4;
+    if (n < 4000000) return true;
+    if (n < kSmallVector)
+        return momentum || grad_bytes <= 8 * saved || pull_bytes >= grad_bytes;
+    return grad_bytes + pull_bytes + saved <= (momentum ? 8 : 6) * saved;
+}
+
 int steps_blocks_per_cu(size_t bytes, size_t n) {
     return bytes <= 8 || (bytes <= 16 && n < 8000000) ? 2 : 1;
 }

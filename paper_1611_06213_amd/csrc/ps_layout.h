@@ -89,6 +89,22 @@ ApplyShape apply_shape(int k, bool momentum, bool bf16, size_t n);
 // fronts choice beyond the phase rule: fronts_log2 is 0).
 ApplyShape sync_shape(int k, bool momentum, bool bf16);
 
+// Whether a script's step that reads grad_bytes of gradients and writes
+// pull_bytes of replicas per coordinate is worth joining to its neighbours in
+// one launch (launch_steps). Joining saves a read and a write of w (and v) and
+// the fan-out's read of w per step, and mixes the replicas' writes with the
+// gradients' reads. Always below 4M coordinates, where launches count too;
+// below kSmallVector with momentum, or unless the gradients dwarf both what is
+// saved and the replicas; from there on if it saves an eighth of the step, a
+// sixth without momentum. Measured from server rows, one launch per call
+// against joined, us a step; with momentum: 1M, 1 gradient and 1 pull 5.1 vs
+// 1.2; 17M, 32 and 16: 570 vs 545; 61M, 16 and 10: 1174 vs 934; 138M, 8 and 8:
+// 1786 vs 1333, 16 and 16: 3133 vs 2705, 32 and 16 (a saving of a tenth):
+// 4400-4607 vs 4486-4510. Without: 4M, 4 and 8: 41 vs 28, 32 and 4: 99 vs 99;
+// 17M, 32 and 4: 414 vs 436, 32 and 32: 711 vs 657; 138M, 8 and 8, every step
+// other replicas (a saving of a seventh): 1597 vs 1673.
+bool steps_join(size_t grad_bytes, size_t pull_bytes, bool momentum, size_t n);
+
 // Resident blocks per compute unit of a launch of several steps (launch_steps)
 // whose steps write `bytes` replica bytes per coordinate each: two while they
 // write little, one beyond (more waves then keep more half-written lines of

@@ -271,11 +271,8 @@ hipError_t run_pull(ps_server *ps, const gadei::PullArgs &a, int dtype, int leve
 // coordinate the whole sequence needs w and v only at its ends. One launch
 // (launch_steps) reads w and v once for several steps, writes the replicas of
 // each from the pass, and a replica that the next step writes again is still
-// in cache then. From server rows with momentum, joined against one launch per
-// call: 1M coordinates, 1 gradient and 1 pull a step 19.7 vs 80.9 us for 16
-// steps; 17M, 8 and 8: 548 vs 936 us for 4; 60M, 32 and 16: 3.53 vs 4.07 ms
-// for 2. No shape measured (100k..60M coordinates, 1..32 gradients, 1..32
-// replicas) was slower joined. A single step's replicas follow fuse_replicas.
+// in cache then. Where that saves enough is steps_join's rule (ps_layout.h); a
+// single step's replicas follow fuse_replicas.
 
 int group_end(const StepGroup &g, int j) {   // replicas written up to gradient j
     return static_cast<int>(g.args.rend[j >> 3] >> (8 * (j & 7))) & 255;
@@ -365,6 +362,13 @@ bool next_step_joins(const StepGroup &g, int r) {
            g.args.r + r + h.pulls + pulls_of(g, h.next) <= PS_MAX_REPLICAS;
 }
 
+// Whether a step of k gradients and r replicas is worth joining to another
+// (steps_join, ps_layout.h).
+bool joining_saves(const ps_server *ps, int k, int grad_dtype, int r, int pull_dtype) {
+    return gadei::steps_join(k * elem_bytes(grad_dtype), r * elem_bytes(pull_dtype),
+                             ps->v != nullptr, ps->n);
+}
+
 // Add the gradients of an apply (one dtype, vector level) to the group,
 // enqueueing what it holds first if they do not fit. A gradient that shares a
 // byte with a replica the group writes must be read after that write, so it
@@ -374,7 +378,9 @@ int join_gradients(ps_server *ps, const PushDesc *d, int count, int gdt) {
     bool fits = g.args.k == 0 ||
                 (g.grad_dtype == gdt && g.args.k + count <= PS_MAX_QUEUE_DEPTH);
     if (fits && g.args.r > 0) {
-        fits = g.args.r + pulls_of(g, g.at) <= PS_MAX_REPLICAS;
+        const int pulls = pulls_of(g, g.at);
+        fits = g.args.r + pulls <= PS_MAX_REPLICAS &&
+               joining_saves(ps, count, gdt, pulls, g.pull_dtype);
         const size_t gb = ps->n * elem_bytes(gdt), rb = ps->n * elem_bytes(g.pull_dtype);
         for (int i = 0; fits && i < count; ++i)
             for (int r = 0; fits && r < g.args.r; ++r)
@@ -411,7 +417,8 @@ bool join_pulls(ps_server *ps, void *const *dsts, int dtype, const std::vector<i
     const bool worth = ps->fuse_max_r >= 0
                            ? r <= ps->fuse_max_r
                            : g.args.r > 0 || gadei::fuse_replicas(r, g.args.k, ps->n) ||
-                                 next_step_joins(g, r);
+                                 (joining_saves(ps, g.args.k, g.grad_dtype, r, dtype) &&
+                                  next_step_joins(g, r));
     if (!worth) return false;
     const size_t rb = ps->n * elem_bytes(dtype), gb = ps->n * elem_bytes(g.grad_dtype);
     for (size_t i = 0; i < write.size(); ++i) {
