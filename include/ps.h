@@ -46,9 +46,9 @@
  *
  * Pointers named "device" must point to device memory (hipMalloc or torch
  * CUDA tensors) on the device that was current at ps_create. Any alignment is
- * accepted and gives identical results: replicas on their elements' boundaries
- * and 16-byte-aligned gradients take the widest vector path, 8-byte-aligned
- * bf16 gradients a narrower one, others a scalar path. Buffers that start on 256-byte (better: 2 MiB) boundaries
+ * accepted and gives identical results: gradients on 4-byte boundaries and
+ * replicas on their elements' boundaries take the vector path, others a
+ * scalar path. Buffers that start on 256-byte (better: 2 MiB) boundaries
  * stream fastest.
  *
  * Status codes: every int-returning call returns PS_OK (0) or a negative

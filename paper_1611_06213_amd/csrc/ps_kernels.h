@@ -68,14 +68,12 @@ struct Shape {
 unsigned blocks_per_cu_lds(int blocks);
 
 // grad_dtype: PS_F32 | PS_BF16. pull_dtype: -1 (no replicas), PS_F32, PS_BF16.
-// level: 2 = every buffer 16-byte aligned; 1 = fp32 buffers 16-byte and bf16
-// buffers 8-byte aligned; 0 = anything else (scalar kernels). The pull has two:
-// 1 = every replica on a boundary of its elements, 0 = scalar.
+// level: 1 = the vector kernels, 0 = the scalar ones (one coordinate per lane;
+// for buffers they can serve no better way, see grad_level and dst_level).
 // shape: residency and group size of the vector kernels (the scalar kernel
-// for misaligned buffers ignores it).
+// ignores it).
 hipError_t launch_apply(const ApplyArgs &a, int grad_dtype, int pull_dtype, int level,
                         const Shape &shape, const Geometry &geo, hipStream_t s);
-// Steps in one launch; every buffer on a boundary the vector kernels take.
 hipError_t launch_steps(const StepsArgs &a, int grad_dtype, int pull_dtype, int blocks_per_cu,
                         const Geometry &geo, hipStream_t s);
 hipError_t launch_pull(const PullArgs &a, int pull_dtype, int level, const Geometry &geo,

@@ -121,7 +121,9 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // The same from any element boundary: gfx950 loads and stores 16 bytes from
-// any address in one instruction.
+// any address in one instruction, at the aligned rate from 4-byte boundaries
+// (17.3M coordinates, K = 32 with momentum, gradient rows at odd fp32
+// offsets: 411 us, 410 at aligned ones; 444 with one coordinate per lane).
 typedef f32x4 f32x4_any __attribute__((aligned(4)));
 typedef u32x2 u32x2_any __attribute__((aligned(2)));
 typedef u32x4 u32x4_any __attribute__((aligned(2)));
@@ -163,8 +165,7 @@ __device__ __forceinline__ float lo_bf16(uint32_t u) { return __uint_as_float(u 
 __device__ __forceinline__ float hi_bf16(uint32_t u) { return __uint_as_float(u & 0xffff0000u); }
 
 // Gradient lanes for coordinates i .. i+E-1 (i is a multiple of E) as
-// loaded: fp32 chunks are 4 values (16 bytes); bf16 chunks are 8 values (16
-// bytes) or 4 (8 bytes) when a buffer is only 8-byte aligned. Gradients are
+// loaded: fp32 chunks are 4 values, bf16 chunks 8 (16 bytes). Gradients are
 // read exactly once per launch, so the loads carry the non-temporal hint.
 // Loading and widening are separate steps so that a group's loads can all be
 // issued before the first of its values is widened.
@@ -172,7 +173,6 @@ template <int GDT, int E> struct GradBits;
 template <> struct GradBits<PS_F32, 4> { f32x4 u; };
 template <> struct GradBits<PS_F32, 1> { float u; };
 template <> struct GradBits<PS_BF16, 8> { u32x4 u; };
-template <> struct GradBits<PS_BF16, 4> { u32x2 u; };
 template <> struct GradBits<PS_BF16, 1> { uint32_t u; };
 
 template <int GDT, int E>
@@ -183,13 +183,12 @@ __device__ __forceinline__ GradBits<GDT, E> ld_bits(const void *g, uint64_t i) {
             r.u = static_cast<const float *>(g)[i];
         } else {
             r.u = __builtin_nontemporal_load(
-                reinterpret_cast<const f32x4 *>(static_cast<const float *>(g) + i));
+                reinterpret_cast<const f32x4_any *>(static_cast<const float *>(g) + i));
         }
     } else {
         if constexpr (E == 8) {
-            r.u = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(g) + (i >> 3));
-        } else if constexpr (E == 4) {
-            r.u = __builtin_nontemporal_load(reinterpret_cast<const u32x2 *>(g) + (i >> 2));
+            r.u = __builtin_nontemporal_load(
+                reinterpret_cast<const u32x4_any *>(static_cast<const uint16_t *>(g) + i));
         } else {
             r.u = static_cast<const uint16_t *>(g)[i];
         }
@@ -211,9 +210,6 @@ __device__ __forceinline__ void widen(float (&x)[E], const GradBits<GDT, E> &r) 
             x[2] = lo_bf16(r.u.y); x[3] = hi_bf16(r.u.y);
             x[4] = lo_bf16(r.u.z); x[5] = hi_bf16(r.u.z);
             x[6] = lo_bf16(r.u.w); x[7] = hi_bf16(r.u.w);
-        } else if constexpr (E == 4) {
-            x[0] = lo_bf16(r.u.x); x[1] = hi_bf16(r.u.x);
-            x[2] = lo_bf16(r.u.y); x[3] = hi_bf16(r.u.y);
         } else {
             x[0] = lo_bf16(r.u);
         }
@@ -752,12 +748,8 @@ hipError_t go_apply(const A &a, int level, const Shape &sh, const Geometry &geo,
     // dynamic LDS that the kernel does not use; 0 blocks = as many as fit.
     const unsigned lds =
         (sh.blocks_per_cu >= 1 && sh.blocks_per_cu <= 4) ? geo.lds_for_blocks[sh.blocks_per_cu] : 0;
-    // bf16 gradients move 16 bytes per lane as 8 values when every buffer is
-    // 16-byte aligned; otherwise (and for fp32) a lane's chunk is 4 values.
-    if constexpr (GDT == PS_BF16) {
-        if (level == 2) return launch_vec_g<MOM, GDT, PDT, 8>(a, sh.group, lds, geo, s);
-    }
-    return launch_vec_g<MOM, GDT, PDT, 4>(a, sh.group, lds, geo, s);
+    // a lane's chunk is 16 bytes of gradient: 8 bf16 or 4 fp32 values
+    return launch_vec_g<MOM, GDT, PDT, GDT == PS_BF16 ? 8 : 4>(a, sh.group, lds, geo, s);
 }
 
 template <bool MOM, int GDT, int E, int G>
@@ -784,10 +776,7 @@ hipError_t go_sync(const ApplyArgs &a, int level, const Shape &sh, const Geometr
     if (level == 0) return launch_sync_vec<MOM, GDT, 1, kGroup>(a, 0, geo, s);
     const unsigned lds =
         (sh.blocks_per_cu >= 1 && sh.blocks_per_cu <= 4) ? geo.lds_for_blocks[sh.blocks_per_cu] : 0;
-    if constexpr (GDT == PS_BF16) {
-        if (level == 2) return launch_sync_g<MOM, GDT, 8>(a, sh.group, lds, geo, s);
-    }
-    return launch_sync_g<MOM, GDT, 4>(a, sh.group, lds, geo, s);
+    return launch_sync_g<MOM, GDT, GDT == PS_BF16 ? 8 : 4>(a, sh.group, lds, geo, s);
 }
 
 template <bool MOM, int GDT, class A>

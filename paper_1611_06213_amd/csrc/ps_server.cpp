@@ -116,18 +116,16 @@ bool aligned(const void *p, size_t a) { return (reinterpret_cast<uintptr_t>(p) %
 
 size_t elem_bytes(int dtype) { return dtype == PS_BF16 ? 2 : 4; }
 
-// Vector level a buffer allows (see launch_apply): 2 if 16-byte aligned, 1 if
-// a bf16 buffer is 8-byte aligned, else 0.
-int level_of(const void *p, int dtype) {
-    if (aligned(p, 16)) return 2;
-    if (dtype == PS_BF16 && aligned(p, 8)) return 1;
-    return 0;
-}
+// Whether the vector kernels (1) may read this gradient, or the scalar ones
+// (0) are to: they take any 4-byte boundary. From the other 2-byte ones, 16-byte
+// loads run at half the rate and one coordinate per lane is faster for bf16
+// (100M coordinates, K = 32 with momentum: 1361 us scalar, 1506 vector; from
+// 4-byte boundaries 1371 vector, 1558 with 8-byte lanes).
+int grad_level(const void *p) { return aligned(p, 4) ? 1 : 0; }
 
-// Whether the fan-outs may write this replica with vector stores (1), or the
-// scalar kernel is to (0): they move their chunks to the replica's own line
-// boundaries (100M coordinates, 16 replicas at odd offsets: fp32 1.39 ms, 2.12
-// scalar; bf16 0.86, 1.39 scalar).
+// The same for a replica: stores take any element boundary (the fan-outs move
+// their chunks to the replica's own line boundaries: 100M coordinates, 16
+// replicas at odd offsets: fp32 1.39 ms, 2.12 scalar; bf16 0.86, 1.39 scalar).
 int dst_level(const void *p, int dtype) { return aligned(p, elem_bytes(dtype)) ? 1 : 0; }
 
 // Whether [p, p + bytes) shares a byte with w or v.
@@ -301,7 +299,7 @@ int flush_group(ps_server *ps) {
         one.fronts_log2 = fronts_for(ps, one, g.grad_dtype);
         const gadei::Shape shape = shape_for(
             ps, gadei::apply_shape(one.k, one.v != nullptr, g.grad_dtype == PS_BF16, one.n));
-        e = run_apply(ps, one, g.grad_dtype, one.r > 0 ? g.pull_dtype : -1, 2, shape, false);
+        e = run_apply(ps, one, g.grad_dtype, one.r > 0 ? g.pull_dtype : -1, 1, shape, false);
     } else {
         const int blocks =
             ps->force_blocks_per_cu >= 0
@@ -337,7 +335,7 @@ Ahead look_ahead(const StepGroup &g, int from, int grad_dtype) {
         const ps_op &o = g.ops[i];
         if (o.kind == PS_OP_PUSH) {
             ++h.pushes;
-            h.same = h.same && o.dtype == grad_dtype && level_of(o.grad, o.dtype) == 2;
+            h.same = h.same && o.dtype == grad_dtype && grad_level(o.grad) == 1;
         } else if (o.kind == PS_OP_PULL) {
             h.pulls += std::max(0, o.count);
         } else {
@@ -465,13 +463,13 @@ int launch_batch(ps_server *ps, const std::vector<PushDesc> &items, int pull_dty
     while (start < q) {
         const int gdt = items[start].dtype;
         size_t end = start;
-        int level = 2;
+        int level = 1;
         while (end < q && items[end].dtype == gdt) {
             a.g[end - start] = items[end].grad;
-            level = std::min(level, level_of(items[end].grad, gdt));
+            level = std::min(level, grad_level(items[end].grad));
             ++end;
         }
-        if (ps->group.open && level == 2) {
+        if (ps->group.open && level == 1) {
             if (int rc = join_gradients(ps, &items[start], static_cast<int>(end - start), gdt))
                 return rc;
             start = end;
@@ -489,7 +487,7 @@ int launch_batch(ps_server *ps, const std::vector<PushDesc> &items, int pull_dty
             a.r = static_cast<int>(write.size());
             for (size_t j = 0; j < write.size(); ++j) {
                 a.dst[j] = dsts[write[j]];
-                level = std::min(level, level_of(a.dst[j], pull_dtype));
+                level = std::min(level, dst_level(a.dst[j], pull_dtype));
             }
         }
         hipError_t e = run_apply(ps, a, gdt, pdt, level, shape, false);
@@ -876,10 +874,10 @@ int ps_apply_sync(ps_server *ps) {
     a.lr = ps->lr;
     a.m = ps->m;
     a.k = static_cast<int>(b.items.size());
-    int level = 2;
+    int level = 1;
     for (size_t j = 0; j < b.items.size(); ++j) {
         a.g[j] = b.items[j].grad;
-        level = std::min(level, level_of(a.g[j], gdt));
+        level = std::min(level, grad_level(a.g[j]));
     }
     a.fronts_log2 = fronts_for(ps, a, -1);   // the phase rule only (no apply_shape)
     const gadei::Shape shape = shape_for(ps, gadei::sync_shape(a.k, a.v != nullptr, gdt == PS_BF16));

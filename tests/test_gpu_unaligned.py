@@ -64,3 +64,40 @@ def test_tiled_fan_outs_at_odd_boundaries(torch, n):
         for j, d in enumerate(dsts):
             assert torch.equal(d.view(ibits), want), (tdt, j)
     srv.close()
+
+
+@pytest.mark.parametrize("rule", ["async", "sync"])
+@pytest.mark.parametrize("gdt", ["f32", "bf16"])
+@pytest.mark.parametrize("n,k", [(1, 1), (7, 9), (1021, 8), (4103, 17), (4103, 33), (20_011, 40)])
+def test_gradients_at_every_boundary(torch, n, k, gdt, rule):
+    """Gradients that are rows of one (k, n) tensor from every start: a launch
+    mixes 16-byte-aligned and element-aligned ones. The replicas written by the
+    apply pass lie at odd elements too."""
+    tdt = torch.float32 if gdt == "f32" else torch.bfloat16
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n + k)
+    for start in range(4 if gdt == "f32" else 8):
+        flat = (torch.randn(k * n + 8, generator=gen, device="cuda") * 1e-2).to(tdt)
+        grads = list(flat[start:start + k * n].view(k, n))
+        w0 = (torch.rand(n, generator=gen, device="cuda") - 0.5) * 0.1
+        dsts = list(torch.zeros((2, n), dtype=tdt, device="cuda"))
+        srv = ps.ParameterServer(n, 0.01, 0.9, queue_depth=k)
+        srv.set_pull_fusion(2)
+        srv.set_weights(w0)
+        o = orc.OracleServer(parity.np_bits(w0), 0.01, 0.9, depth=k)
+        for j, g in enumerate(grads):
+            assert srv.push(j % 5, g)
+            o.push(j % 5, parity.np_bits(g))
+        if rule == "sync":
+            srv.apply_sync()
+            srv.pull_many([0, 1], dsts)
+            o.apply_sync()
+        else:
+            srv.apply_pull([0, 1], dsts)
+            o.apply_pending()
+        o.pull(0, 0, ps.PS_F32 if gdt == "f32" else ps.PS_BF16)
+        assert parity.bitwise(parity.np_bits(srv.weights_copy()), o.w), start
+        assert parity.bitwise(parity.np_bits(srv.velocity_copy()), o.v), start
+        for d in dsts:
+            assert parity.bitwise(parity.np_bits(d), o.replicas[0]), start
+        srv.close()
