@@ -421,8 +421,8 @@ int ps_run(ps_server *ps, const ps_op *ops, int count, int *done);
  *
  * ps_graph_launch: the calls again, planned and committed on the host as
  * by ps_run (timestamps, staleness, pull history, statistics), and the graph
- * enqueued on the server's stream, ordered with every other call. The
- * result is identical to ps_run of the same script. Every launch checks that
+ * (its kernels one by one when they are few, which enqueues faster) enqueued
+ * on the server's stream, ordered with every other call. The result is identical to ps_run of the same script. Every launch checks that
  * the calls would now launch exactly the captured kernels (same buffers,
  * gradients per apply, replicas written, launch shapes); if not -- say a
  * pull that was written at capture would now be skipped -- it returns
