@@ -56,6 +56,33 @@ def build_all(verbose: bool = False):
     return build(verbose), build(verbose, out=LIB_FMA, extra=FMA_FLAGS)
 
 
+# the Python binding's per-step calls (host only; needs torch's headers)
+BINDING_SRC = os.path.join(CSRC, "ps_binding.cpp")
+BINDING = os.path.join(HERE, "_binding.so")
+
+
+def build_binding(verbose: bool = False) -> str:
+    import sysconfig
+
+    import torch
+    t = os.path.dirname(torch.__file__)
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I", INCLUDE,
+           "-isystem", os.path.join(t, "include"),
+           "-isystem", os.path.join(t, "include", "torch", "csrc", "api", "include"),
+           "-isystem", sysconfig.get_paths()["include"], BINDING_SRC,
+           "-L", os.path.join(t, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10",
+           "-o", BINDING + ".tmp"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        sys.stderr.write(r.stdout + r.stderr)
+        raise RuntimeError("g++ failed building the Python binding")
+    os.replace(BINDING + ".tmp", BINDING)
+    return BINDING
+
+
 # a plain C program that drives the C ABI without Python (tests/test_c_abi.py)
 C_SMOKE_SRC = os.path.join(ROOT, "tests", "c_abi_smoke.c")
 C_SMOKE = os.path.join(ROOT, "tests", "c_abi_smoke")
@@ -79,4 +106,4 @@ def build_c_smoke(verbose: bool = False) -> str:
 
 
 if __name__ == "__main__":
-    print(build_all(verbose=True))
+    print(build_all(verbose=True), build_binding(verbose=True))

@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
 import threading
 from collections import deque
 from typing import Optional, Sequence
@@ -146,6 +147,28 @@ def load_library(path: Optional[str] = None):
     if path is None:
         _lib = L
     return L
+
+
+_native = None
+
+
+def load_binding():
+    """The native side of ParameterServer's per-step calls (once). Raises if
+    it is not built."""
+    global _native
+    if _native is None:
+        path = os.path.join(_HERE, "_binding.so")
+        if not os.path.exists(path):
+            raise RuntimeError(f"{path} is not built: run "
+                               "`python -c 'import __graft_entry__ as g; g.build()'`")
+        import torch  # noqa: F401  (the module links against its libraries)
+        from . import _binding
+        _native = _binding
+    return _native
+
+
+def _address(f) -> int:
+    return ctypes.cast(f, _VP).value
 
 
 class PSError(RuntimeError):
@@ -416,13 +439,18 @@ def ps_get_stats(h: int):
 
 # ------------------------------------------------------------ tensor wrapper
 
+_codes = None   # torch dtype -> PS_F32 | PS_BF16, once torch is loaded
+
+
 def _dtype_code(t) -> int:
-    import torch
-    if t.dtype == torch.float32:
-        return PS_F32
-    if t.dtype == torch.bfloat16:
-        return PS_BF16
-    raise TypeError(f"unsupported dtype {t.dtype}")
+    global _codes
+    if _codes is None:
+        import torch
+        _codes = {torch.float32: PS_F32, torch.bfloat16: PS_BF16}
+    code = _codes.get(t.dtype)
+    if code is None:
+        raise TypeError(f"unsupported dtype {t.dtype}")
+    return code
 
 
 class ParameterServer:
@@ -446,6 +474,15 @@ class ParameterServer:
         self._lock = threading.RLock()
         self._pending = {}   # learner id -> deque of pushed tensors, oldest first
         self._streams = []   # torch streams the device work may run on (set_stream, set_pull_stream)
+        self._packed_streams = b""   # of _streams, for the native calls
+        # what push, pull and apply call on every step, looked up once
+        self._lib = load_library()
+        native = load_binding()
+        self._native_push, self._native_pulls = native.push, native.pulls
+        self._push_fn = _address(self._lib.ps_push_dtype)
+        self._pull_many_fn = _address(self._lib.ps_pull_many)
+        self._apply_pull_fn = _address(self._lib.ps_apply_pull)
+        self._applied = (ctypes.c_int * PS_MAX_QUEUE_DEPTH)()   # of ps_last_applied, under _lock
         if queue_depth is not None:
             self._check(ps_set_queue_depth(self.h, queue_depth), "set_queue_depth")
         if stream is not None:
@@ -477,6 +514,8 @@ class ParameterServer:
     def _track(self, stream) -> None:
         if stream is not None and not isinstance(stream, int) and stream not in self._streams:
             self._streams.append(stream)
+            self._packed_streams += struct.pack("=3q", stream.stream_id, stream.device_index,
+                                                stream.device_type)
 
     def _uses(self, t) -> None:
         """Tell torch's caching allocator that the server's streams use `t`,
@@ -521,14 +560,18 @@ class ParameterServer:
 
     def push(self, learner: int, grad) -> bool:
         """Enqueue; False when the queue is full (nothing enqueued)."""
-        ptr, code = self._tensor(grad, "push"), _dtype_code(grad)
         with self._lock:
-            rc = ps_push_dtype(self.h, learner, ptr, code)
+            rc = self._native_push(self._push_fn, self.h, learner, grad, self.n,
+                                   self._packed_streams)
+            if rc is None:   # not a plain tensor of the server's size
+                ptr, code = self._tensor(grad, "push"), _dtype_code(grad)
+                rc = ps_push_dtype(self.h, learner, ptr, code)
+                if rc == PS_OK:
+                    self._uses(grad)
             if rc == PS_EFULL:
                 return False
             self._check(rc, "push")
-            self._uses(grad)
-            self._pending.setdefault(learner, deque()).append(grad)
+            self._keep(learner, grad)
         return True
 
     def push_async(self, learner: int, grad, ready_event) -> bool:
@@ -541,22 +584,32 @@ class ParameterServer:
                 return False
             self._check(rc, "push_async")
             self._uses(grad)
-            self._pending.setdefault(learner, deque()).append((grad, ready_event))
+            self._keep(learner, (grad, ready_event))
         return True
+
+    def _keep(self, learner: int, item) -> None:
+        """Keep an enqueued gradient referenced until its apply. Caller holds
+        the lock."""
+        q = self._pending.get(learner)
+        if q is None:
+            q = self._pending[learner] = deque()
+        q.append(item)
 
     def _release_applied(self) -> None:
         """Drop the references of the gradients the last apply consumed: per
         learner the oldest ones (every queue mode keeps each learner's pushes
         in order), as many as ps_last_applied names. Caller holds the lock."""
-        ids = ps_last_applied(self.h)
-        if isinstance(ids, int):
-            self._check(ids, "last_applied")
-        for l in ids:
-            q = self._pending.get(l)
+        ids = self._applied
+        count = self._lib.ps_last_applied(self.h, ids, PS_MAX_QUEUE_DEPTH)
+        if count < 0:
+            self._check(count, "last_applied")
+        pending = self._pending
+        for l in ids[:count]:
+            q = pending.get(l)
             if q:
                 q.popleft()
                 if not q:
-                    del self._pending[l]
+                    del pending[l]
 
     def record(self, event) -> None:
         """Record a torch.cuda.Event on the server's stream."""
@@ -573,12 +626,12 @@ class ParameterServer:
 
     def apply_pending(self) -> None:
         with self._lock:
-            self._check(ps_apply_pending(self.h), "apply_pending")
+            self._check(self._lib.ps_apply_pending(self.h), "apply_pending")
             self._release_applied()
 
     def apply_sync(self) -> None:
         with self._lock:
-            self._check(ps_apply_sync(self.h), "apply_sync")
+            self._check(self._lib.ps_apply_sync(self.h), "apply_sync")
             self._release_applied()
 
     def pull(self, learner: int, dst) -> None:
@@ -597,13 +650,21 @@ class ParameterServer:
         return ptrs, (codes.pop() if codes else PS_F32)
 
     def pull_many(self, learners: Sequence[int], dsts) -> None:
-        ptrs, dt = self._replicas(learners, dsts, "pull_many")
-        self._check(ps_pull_many(self.h, list(learners), ptrs, dt), "pull_many")
+        rc = self._native_pulls(self._pull_many_fn, self.h, learners, dsts, self.n,
+                                self._packed_streams)
+        if rc is None:   # not plain tensors of the server's size
+            ptrs, dt = self._replicas(learners, dsts, "pull_many")
+            rc = ps_pull_many(self.h, list(learners), ptrs, dt)
+        self._check(rc, "pull_many")
 
     def apply_pull(self, learners: Sequence[int], dsts) -> None:
-        ptrs, dt = self._replicas(learners, dsts, "apply_pull")
         with self._lock:
-            self._check(ps_apply_pull(self.h, list(learners), ptrs, dt), "apply_pull")
+            rc = self._native_pulls(self._apply_pull_fn, self.h, learners, dsts, self.n,
+                                    self._packed_streams)
+            if rc is None:
+                ptrs, dt = self._replicas(learners, dsts, "apply_pull")
+                rc = ps_apply_pull(self.h, list(learners), ptrs, dt)
+            self._check(rc, "apply_pull")
             self._release_applied()
 
     def retire_learner(self, learner: int) -> int:
