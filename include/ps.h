@@ -191,9 +191,9 @@ int ps_apply_pull(ps_server *ps, int n, const int *learner_ids, void *const *dst
 
 /* Largest replica count ps_apply_pull writes from the apply pass itself
  * (0..PS_MAX_REPLICAS), or -1 (default) to choose per call: one replica
- * always, up to 4 when the apply folds at most 16 gradients, up to 6 when it
- * folds at most 8 into a vector of fewer than 20M coordinates (measured
- * faster there; with more gradients or replicas the separate fan-out is).
+ * always, up to 4 when the apply folds at most 16 gradients, more for vectors
+ * of fewer than 20M coordinates and all for the smallest (where measured
+ * faster; with more gradients or replicas the separate fan-out is).
  * In a script (ps_run, graphs) a limit of 0 or more holds for every pull that
  * would otherwise be written together with the applies around it.
  * Results are identical either way. PS_EINVAL for other values. */

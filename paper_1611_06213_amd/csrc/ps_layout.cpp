@@ -43,7 +43,34 @@ int fronts_log2_for(const void *const *ptrs, int count) {
     return (streams >= 8 && 2 * most > streams) ? 2 : 0;
 }
 
+namespace {
+
+// apply_shape below kMidVector coordinates. Measured at 100k, 1M and 4M for
+// the depths 1, 2, 4, 8, 16, 32 and 64; the depths between take a neighbour's.
+ApplyShape small_apply_shape(int k, bool momentum, bool bf16, size_t n) {
+    const bool tiny = n < kTinyVector;
+    if (bf16) {
+        if (k <= 11 && !momentum) return {k <= 2 ? 4 : 3, 0, 8};
+        if (k <= 23 || tiny) return {2, 0, 16};
+        return {2, 0, 4};
+    }
+    if (momentum) {
+        if (k <= 1) return {4, 0, 16};
+        if (k <= 9) return {0, 0, 16};
+        if (k <= 13) return {2, 0, 12};
+        if (k <= 31) return {2, 0, 16};
+        if (k <= 47 && !tiny) return {2, 0, 4};
+        return {1, 0, 32};
+    }
+    if (k <= 9) return {0, 0, 16};
+    if (k <= 31) return {2, 0, 16};
+    return {1, 0, 32};
+}
+
+}  // namespace
+
 ApplyShape apply_shape(int k, bool momentum, bool bf16, size_t n) {
+    if (n < kMidVector) return small_apply_shape(k, momentum, bf16, n);
     // Measured at 138,357,544 fp32 / 200,000,000 bf16 parameters for the
     // depths 1, 2, 3, 4, 6, 8, 12, 16, 20, 24, 32, 36, 40, 44, 48 and 64
     // (bf16: from 8); the depths between take a neighbour's shape. A group of
@@ -127,7 +154,10 @@ int steps_blocks_per_cu(size_t bytes, size_t n) {
 }
 
 bool fuse_replicas(int r, int k, size_t n) {
-    return r <= 1 || (r <= 4 && k <= 16) || (r <= 6 && k <= 8 && n < kSmallVector);
+    if (r <= 1 || (r <= 4 && k <= 16) || (r <= 6 && k <= 8 && n < kSmallVector)) return true;
+    if (n < kTinyVector) return true;
+    if (n < 1500000) return r <= 4 || r * k <= 128;
+    return n < 3000000 && r <= 8 && k <= 16;
 }
 
 }  // namespace gadei

@@ -83,6 +83,16 @@ struct ApplyShape {
 // of two (Text-CNN-sized vectors, 10M and 17.3M: 77.3-77.7 and 76.2% vs
 // 76.2-76.4 and 74.7; from 24M two are best, 80.4 vs 79.2).
 constexpr size_t kSmallVector = 20000000;
+// Below kMidVector a launch is a few waves of blocks or less and what counts
+// is the latency of its first loads, not DRAM pages: more blocks or a larger
+// group at once (kernel time, from the table of large vectors to this one; 1M:
+// fp32 with momentum k = 4 7.8 -> 6.9 us, 16 16.1 -> 14.9; bf16 with momentum
+// k = 32 17.8 -> 15.0; bf16 k = 64 25.9 -> 22.8; 4M: fp32 with momentum k = 16
+// 54.8 -> 51.7, bf16 with momentum k = 64 98.8 -> 89.8). At 7M the two are
+// within 5% of each other either way. Below kTinyVector one round of blocks holds everything, and all of a
+// lane's loads go out together (100k, fp32 k = 64: 10.2 -> 8.4 us).
+constexpr size_t kMidVector = 5000000;
+constexpr size_t kTinyVector = 500000;
 ApplyShape apply_shape(int k, bool momentum, bool bf16, size_t n);
 
 // The same for a synchronous step over k gradients (one per learner; no
@@ -121,7 +131,13 @@ int steps_blocks_per_cu(size_t bytes, size_t n);
 // folded; up to 6 when at most 8 are folded into a vector of fewer than
 // kSmallVector coordinates (10M, k = 8: r = 5 0.100 vs 0.104 ms, r = 6 0.108
 // vs 0.110; at 30M and above 5 or 6 are even or slower, 138M r = 6 1.50 vs
-// 1.44 ms). Writing replicas from
+// 1.44 ms). For smaller vectors the fan-out's launch weighs more (apply+pull
+// with momentum, fused vs separate): below 3M up to 8 when at most 16 are
+// folded (2M: k = 1, r = 8 19.1 vs 21.5 us; k = 8, r = 8 28.9 vs 29.4; 4M: k = 8,
+// r = 8 54.9 vs 54.3); below 1.5M as long as there are few of one or the
+// other (1M: k = 1, r = 16 14.2 vs 16.0; k = 32, r = 4 28.4 vs 30.0, r = 16 36.9
+// vs 35.1); below kTinyVector always (100k: k = 1, r = 2 5.5 vs 8.1; k = 32, r =
+// 16 30.0 vs 33.5). Writing replicas from
 // the apply adds write streams to its read streams, which costs more than a
 // separate fan-out once there are many of either; for few of both it saves
 // the fan-out's launch and its second read of w. Measured from server rows

@@ -283,6 +283,27 @@ def test_apply_shape_table(driver):
     assert got == [f"shape {x} {y} {z}" for (x, y, z) in small.values()]
 
 
+def test_small_vector_rules(driver):
+    """Below 5M coordinates applies of every depth get a shape the launcher
+    supports, with groups above 16 only where the depth fills them; replicas
+    join the apply more freely the smaller the vector."""
+    for n in (1, 499_999, 500_000, 4_999_999):
+        cases = [(k, m, b) for k in range(1, 65) for m in (0, 1) for b in (0, 1)]
+        out = run_driver(driver, [f"shape {k} {m} {b} {n}" for (k, m, b) in cases])
+        for (k, _, _), line in zip(cases, out):
+            b, f, g = map(int, line.split()[1:])
+            assert 0 <= b <= 4 and f == 0 and g in (4, 8, 12, 16, 24, 32) and (g <= 16 or g <= k)
+    edge = {(16, 1, 0, 4_999_999): (2, 0, 16), (16, 1, 0, 5_000_000): (1, 0, 16),
+            (32, 1, 0, 500_000): (2, 0, 4), (32, 1, 0, 499_999): (1, 0, 32)}
+    got = run_driver(driver, [f"shape {k} {m} {b} {n}" for (k, m, b, n) in edge])
+    assert got == [f"shape {x} {y} {z}" for (x, y, z) in edge.values()]
+    fuse = {(64, 64, 499_999): 1, (16, 8, 1_499_999): 1, (16, 9, 1_499_999): 0,
+            (4, 64, 1_499_999): 1, (8, 16, 2_999_999): 1, (9, 16, 2_999_999): 0,
+            (8, 17, 2_999_999): 0, (8, 16, 3_000_000): 0}
+    got = run_driver(driver, [f"fuse {r} {k} {n}" for (r, k, n) in fuse])
+    assert got == [f"fuse {v}" for v in fuse.values()]
+
+
 def test_replica_fusion_rule(driver):
     """ps_apply_pull writes one replica from the apply pass always, up to 4
     when the apply folds at most 16 gradients, up to 6 when it folds at most 8
