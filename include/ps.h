@@ -245,7 +245,8 @@ int ps_set_queue_mode(ps_server *ps, int mode, int slots_per_learner);
 
 /* How the apply kernels sweep the weights: 2^fronts_log2 evenly spaced
  * fronts (0..3), or -1 (default) to choose per apply from the buffers'
- * offsets within 2 MiB -- four fronts when at least 8 buffers take part and
+ * offsets within 2 MiB -- four fronts for gradients of 500 MB and more when at
+ * least 8 buffers take part and
  * more than half of the gradient, w and v buffers share one 4 KiB offset (as
  * separately allocated, 2 MiB-aligned buffers do), one front otherwise
  * (ps_alloc_rows buffers). Results are identical either way; only the

@@ -187,21 +187,18 @@ int drain_pulls(ps_server *ps) {
     return PS_OK;
 }
 
-// Fronts for an apply over a.g[0..k) of dtype gdt (-1: no shape table), w
-// and v: the server's setting, or chosen from the buffers' offsets
-// (fronts_log2_for), and for buffers at distinct offsets from the apply's
-// shape (apply_shape).
+// Fronts for an apply or synchronous step over a.g[0..k) of dtype gdt, w and
+// v: the server's setting, or chosen from the buffers' offsets and length
+// (fronts_log2_for, kFrontsBytes).
 int fronts_for(const ps_server *ps, const gadei::ApplyArgs &a, int gdt) {
     if (ps->geo.fronts_log2 >= 0) return ps->geo.fronts_log2;
+    if (a.n * elem_bytes(gdt) < gadei::kFrontsBytes) return 0;
     const void *p[PS_MAX_QUEUE_DEPTH + 2];
     int c = 0;
     for (int j = 0; j < a.k; ++j) p[c++] = a.g[j];
     p[c++] = a.w;
     p[c++] = a.v;   // null without momentum: not a stream
-    const int f = gadei::fronts_log2_for(p, c);
-    if (f == 0 && gdt >= 0)
-        return gadei::apply_shape(a.k, a.v != nullptr, gdt == PS_BF16, a.n).fronts_log2;
-    return f;
+    return gadei::fronts_log2_for(p, c);
 }
 
 // The launch shape for a table entry, with the caller's overrides.
@@ -910,7 +907,7 @@ int ps_apply_sync(ps_server *ps) {
         a.g[j] = b.items[j].grad;
         level = std::min(level, grad_level(a.g[j]));
     }
-    a.fronts_log2 = fronts_for(ps, a, -1);   // the phase rule only (no apply_shape)
+    a.fronts_log2 = fronts_for(ps, a, gdt);
     const gadei::Shape shape = shape_for(ps, gadei::sync_shape(a.k, a.v != nullptr, gdt == PS_BF16));
     hipError_t e = run_apply(ps, a, gdt, -1, level, shape, true);
     if (e != hipSuccess) return fail_hip(e, "synchronous step launch");
