@@ -245,11 +245,10 @@ int ps_set_queue_mode(ps_server *ps, int mode, int slots_per_learner);
 
 /* How the apply kernels sweep the weights: 2^fronts_log2 evenly spaced
  * fronts (0..3), or -1 (default) to choose per apply from the buffers'
- * offsets within 2 MiB -- four fronts for gradients of 500 MB and more when at
- * least 8 buffers take part and
- * more than half of the gradient, w and v buffers share one 4 KiB offset (as
- * separately allocated, 2 MiB-aligned buffers do), one front otherwise
- * (ps_alloc_rows buffers). Results are identical either way; only the
+ * offsets within 2 MiB and their length -- four fronts for gradients of 500 MB
+ * and more when at least 8 buffers take part and more than half of the
+ * gradient, w and v buffers share one 4 KiB offset (as separately allocated,
+ * 2 MiB-aligned buffers do), one front otherwise (ps_alloc_rows buffers). Results are identical either way; only the
  * order in which the grid visits coordinates changes. */
 int ps_set_fronts(ps_server *ps, int fronts_log2);
 
@@ -402,8 +401,8 @@ typedef struct ps_op {
  * schedule without a host-language round trip per call. Stops at the first
  * call that does not return PS_OK (a full queue included) and returns its
  * status; *done (may be NULL) receives the number of calls completed.
- * Consecutive applies and the pulls between them may go out as one kernel
- * launch (up to PS_MAX_QUEUE_DEPTH gradients and PS_MAX_REPLICAS replicas),
+ * Consecutive applies, or consecutive synchronous steps, and the pulls between
+ * them may go out as one kernel launch (up to PS_MAX_QUEUE_DEPTH gradients and PS_MAX_REPLICAS replicas),
  * with the same results; every kernel has been enqueued when ps_run returns.
  * If such a launch fails (PS_EHIP), *done counts the calls before the ones
  * that went out in it.

@@ -26,9 +26,11 @@ struct ApplyArgs {
 };
 
 // Several steps in one pass: gradients 0..k-1 in order, and after gradient j
-// the replicas dst[e(j-1)] .. dst[e(j)-1], where e(j) is byte j of rend (byte
-// j % 8, least significant first, of word j / 8; not decreasing, and r for the
-// last gradient).
+// the replicas dst[e(j-1)] .. dst[e(j)-1]. Byte j of rend (byte j % 8, least
+// significant first, of word j / 8) holds e(j) in its low seven bits, not
+// decreasing and r for the last gradient; synchronous steps also mark the last
+// gradient of each with kLastOfStep.
+constexpr int kLastOfStep = 128;
 struct StepsArgs : ApplyArgs {
     uint64_t rend[PS_MAX_QUEUE_DEPTH / 8];
     uint64_t again;   // bit r: dst[r] is the buffer of a later replica too
@@ -74,8 +76,10 @@ unsigned blocks_per_cu_lds(int blocks);
 // ignores it).
 hipError_t launch_apply(const ApplyArgs &a, int grad_dtype, int pull_dtype, int level,
                         const Shape &shape, const Geometry &geo, hipStream_t s);
-hipError_t launch_steps(const StepsArgs &a, int grad_dtype, int pull_dtype, int blocks_per_cu,
-                        const Geometry &geo, hipStream_t s);
+// sync: each step averages its gradients (launch_sync), else one step per
+// gradient.
+hipError_t launch_steps(const StepsArgs &a, bool sync, int grad_dtype, int pull_dtype,
+                        int blocks_per_cu, const Geometry &geo, hipStream_t s);
 hipError_t launch_pull(const PullArgs &a, int pull_dtype, int level, const Geometry &geo,
                        hipStream_t s);
 // Synchronous step over a.k gradients of one dtype (no replicas).

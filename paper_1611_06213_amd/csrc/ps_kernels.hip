@@ -454,17 +454,27 @@ __global__ void __launch_bounds__(kBlock) apply_vec(const A a) {
 template <class A>
 using KernArgs = const A __attribute__((address_space(4))) *;
 
+// What a lane carries through a run of steps: its coordinates, the replicas
+// written so far and, for synchronous steps, the sum of the step's gradients
+// and their number.
+template <int E>
+struct StepsLane {
+    float w[E], v[E], s[E];
+    int r, count;
+};
+
 // Gradients k0 .. k0+G-1 of a run of steps (G at most 8, or 16), each
-// followed by the replicas pulled after it: as apply_group, with the stores
+// followed by the replicas pulled after it: as apply_group (SYNC: sum_group,
+// with the averaged step after the last gradient of each), with the stores
 // of dst[r] .. between the updates. A replica that a later step of this
 // launch writes again is stored with the ordinary policy, so that its line is
 // still in L2 then and reaches HBM once (16 steps of 4 gradients and the same
 // 4 replicas, 4M coordinates: 243 us, 361 with the non-temporal hint); the
 // last write of each carries the hint (all plain: up to 5% slower where
 // every step writes other replicas).
-template <bool MOM, int GDT, int PDT, int E, int G, class A>
-__device__ __forceinline__ void steps_group(KernArgs<A> a, int k0, uint64_t i, float (&w)[E],
-                                            float (&v)[E], float lr, float m, int &r) {
+template <bool SYNC, bool MOM, int GDT, int PDT, int E, int G, class A>
+__device__ __forceinline__ void steps_group(KernArgs<A> a, int k0, uint64_t i, StepsLane<E> &l,
+                                            float lr, float m) {
     GradBits<GDT, E> b[G];
 #pragma unroll
     for (int j = 0; j < G; ++j) b[j] = ld_bits<GDT, E>(a->g[k0 + j], i);
@@ -475,65 +485,95 @@ __device__ __forceinline__ void steps_group(KernArgs<A> a, int k0, uint64_t i, f
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int j = 0; j < G; ++j) {
+        const int mark = static_cast<int>(ends[j >> 3] >> (8 * (j & 7))) & 255;
         float g[E];
         widen<GDT, E>(g, b[j]);
-        step<MOM, E>(w, v, g, lr, m);
-        const int end = static_cast<int>(ends[j >> 3] >> (8 * (j & 7))) & 255;
-        for (; r < end; ++r) {
-            if ((again >> r) & 1) {
-                st_dst<PDT, E, false>(a->dst[r], i, w);
+        if constexpr (SYNC) {
+#pragma unroll
+            for (int e = 0; e < E; ++e) l.s[e] = l.s[e] + g[e];
+            ++l.count;
+            if (mark & kLastOfStep) {
+                const float kf = static_cast<float>(l.count);
+#pragma unroll
+                for (int e = 0; e < E; ++e) {
+                    g[e] = l.s[e] / kf;
+                    l.s[e] = 0.0f;
+                }
+                l.count = 0;
+                step<MOM, E>(l.w, l.v, g, lr, m);
+            }
+        } else {
+            step<MOM, E>(l.w, l.v, g, lr, m);
+        }
+        for (const int end = mark & (kLastOfStep - 1); l.r < end; ++l.r) {
+            if ((again >> l.r) & 1) {
+                st_dst<PDT, E, false>(a->dst[l.r], i, l.w);
                 asm volatile("");   // or the compiler makes the two stores one, without the hint
             } else {
-                st_dst<PDT, E>(a->dst[r], i, w);
+                st_dst<PDT, E>(a->dst[l.r], i, l.w);
             }
         }
     }
 }
 
-template <bool MOM, int GDT, int PDT, int E, class A>
+template <bool SYNC, bool MOM, int GDT, int PDT, int E, class A>
 __device__ __forceinline__ void steps_chunk(KernArgs<A> a, uint64_t i) {
     // 16 gradients' loads at once (8: 0-8% slower; 24: within 1%)
     constexpr int G = sizeof(A::rend) == 8 ? 8 : 16;
-    float w[E], v[E];
-    ld_f32<E, nt_wv_ld<E>()>(w, a->w + i);
-    if constexpr (MOM) ld_f32<E, nt_wv_ld<E>()>(v, a->v + i);
+    StepsLane<E> l;
+    ld_f32<E, nt_wv_ld<E>()>(l.w, a->w + i);
+    if constexpr (MOM) ld_f32<E, nt_wv_ld<E>()>(l.v, a->v + i);
+#pragma unroll
+    for (int e = 0; e < E; ++e) l.s[e] = 0.0f;
+    l.r = 0;
+    l.count = 0;
     const float lr = a->lr;
     const float m = a->m;
     const int k = a->k;
-    int r = 0, k0 = 0;
+    int k0 = 0;
     if (k >= G) {
-        steps_group<MOM, GDT, PDT, E, G, A>(a, 0, i, w, v, lr, m, r);
+        steps_group<SYNC, MOM, GDT, PDT, E, G, A>(a, 0, i, l, lr, m);
         k0 = G;
     }
-    for (; k0 + G <= k; k0 += G) steps_group<MOM, GDT, PDT, E, G, A>(a, k0, i, w, v, lr, m, r);
+    for (; k0 + G <= k; k0 += G) steps_group<SYNC, MOM, GDT, PDT, E, G, A>(a, k0, i, l, lr, m);
     if constexpr (G > 8) {
         if (k0 + 8 <= k) {
-            steps_group<MOM, GDT, PDT, E, 8, A>(a, k0, i, w, v, lr, m, r);
+            steps_group<SYNC, MOM, GDT, PDT, E, 8, A>(a, k0, i, l, lr, m);
             k0 += 8;
         }
     }
     switch (k - k0) {
-        case 1: steps_group<MOM, GDT, PDT, E, 1, A>(a, k0, i, w, v, lr, m, r); break;
-        case 2: steps_group<MOM, GDT, PDT, E, 2, A>(a, k0, i, w, v, lr, m, r); break;
-        case 3: steps_group<MOM, GDT, PDT, E, 3, A>(a, k0, i, w, v, lr, m, r); break;
-        case 4: steps_group<MOM, GDT, PDT, E, 4, A>(a, k0, i, w, v, lr, m, r); break;
-        case 5: steps_group<MOM, GDT, PDT, E, 5, A>(a, k0, i, w, v, lr, m, r); break;
-        case 6: steps_group<MOM, GDT, PDT, E, 6, A>(a, k0, i, w, v, lr, m, r); break;
-        case 7: steps_group<MOM, GDT, PDT, E, 7, A>(a, k0, i, w, v, lr, m, r); break;
+        case 1: steps_group<SYNC, MOM, GDT, PDT, E, 1, A>(a, k0, i, l, lr, m); break;
+        case 2: steps_group<SYNC, MOM, GDT, PDT, E, 2, A>(a, k0, i, l, lr, m); break;
+        case 3: steps_group<SYNC, MOM, GDT, PDT, E, 3, A>(a, k0, i, l, lr, m); break;
+        case 4: steps_group<SYNC, MOM, GDT, PDT, E, 4, A>(a, k0, i, l, lr, m); break;
+        case 5: steps_group<SYNC, MOM, GDT, PDT, E, 5, A>(a, k0, i, l, lr, m); break;
+        case 6: steps_group<SYNC, MOM, GDT, PDT, E, 6, A>(a, k0, i, l, lr, m); break;
+        case 7: steps_group<SYNC, MOM, GDT, PDT, E, 7, A>(a, k0, i, l, lr, m); break;
         default: break;
     }
-    st_f32<E, nt_wv_st<E>()>(a->w + i, w);
-    if constexpr (MOM) st_f32<E, nt_wv_st<E>()>(a->v + i, v);
+    st_f32<E, nt_wv_st<E>()>(a->w + i, l.w);
+    if constexpr (MOM) st_f32<E, nt_wv_st<E>()>(a->v + i, l.v);
 }
 
-template <bool MOM, int GDT, int PDT, int E, class A>
-__global__ void __launch_bounds__(kBlock) apply_vec_steps(const A) {
+template <bool SYNC, bool MOM, int GDT, int PDT, int E, class A>
+__device__ __forceinline__ void steps_sweep() {
     const KernArgs<A> a = (KernArgs<A>)__builtin_amdgcn_kernarg_segment_ptr();
     const uint64_t chunks = a->n / E;
     const uint64_t tid = static_cast<uint64_t>(blockIdx.x) * kBlock + threadIdx.x;
     const uint64_t stride = static_cast<uint64_t>(gridDim.x) * kBlock;
-    for (uint64_t c = tid; c < chunks; c += stride) steps_chunk<MOM, GDT, PDT, E, A>(a, c * E);
-    if (tid < a->n - chunks * E) steps_chunk<MOM, GDT, PDT, 1, A>(a, chunks * E + tid);
+    for (uint64_t c = tid; c < chunks; c += stride) steps_chunk<SYNC, MOM, GDT, PDT, E, A>(a, c * E);
+    if (tid < a->n - chunks * E) steps_chunk<SYNC, MOM, GDT, PDT, 1, A>(a, chunks * E + tid);
+}
+
+template <bool MOM, int GDT, int PDT, int E, class A>
+__global__ void __launch_bounds__(kBlock) apply_vec_steps(const A) {
+    steps_sweep<false, MOM, GDT, PDT, E, A>();
+}
+
+template <bool MOM, int GDT, int PDT, int E, class A>
+__global__ void __launch_bounds__(kBlock) sync_vec_steps(const A) {
+    steps_sweep<true, MOM, GDT, PDT, E, A>();
 }
 
 // Scalar path for buffers without vector alignment: one coordinate per lane.
@@ -825,28 +865,29 @@ hipError_t launch_apply(const ApplyArgs &a, int grad_dtype, int pull_dtype, int 
     return go_apply_g<false>(a, grad_dtype, pull_dtype, level, shape, geo, s);
 }
 
-template <bool MOM, class A>
-hipError_t go_steps(const A &a, int gdt, int pdt, unsigned lds, const Geometry &geo,
-                    hipStream_t s) {
-    const dim3 block(kBlock);
-    if (gdt == PS_F32) {
-        const dim3 grid(grid_for(a.n / 4, geo));
-        if (pdt == PS_F32)
-            hipLaunchKernelGGL((apply_vec_steps<MOM, PS_F32, PS_F32, 4, A>), grid, block, lds, s, a);
-        else
-            hipLaunchKernelGGL((apply_vec_steps<MOM, PS_F32, PS_BF16, 4, A>), grid, block, lds, s, a);
-    } else {
-        const dim3 grid(grid_for(a.n / 8, geo));
-        if (pdt == PS_F32)
-            hipLaunchKernelGGL((apply_vec_steps<MOM, PS_BF16, PS_F32, 8, A>), grid, block, lds, s, a);
-        else
-            hipLaunchKernelGGL((apply_vec_steps<MOM, PS_BF16, PS_BF16, 8, A>), grid, block, lds, s, a);
-    }
+template <bool MOM, int GDT, int PDT, class A>
+hipError_t go_steps_p(const A &a, bool sync, unsigned lds, const Geometry &geo, hipStream_t s) {
+    constexpr int E = GDT == PS_BF16 ? 8 : 4;
+    const dim3 grid(grid_for(a.n / E, geo));
+    if (sync)
+        hipLaunchKernelGGL((sync_vec_steps<MOM, GDT, PDT, E, A>), grid, dim3(kBlock), lds, s, a);
+    else
+        hipLaunchKernelGGL((apply_vec_steps<MOM, GDT, PDT, E, A>), grid, dim3(kBlock), lds, s, a);
     return hipGetLastError();
 }
 
-hipError_t launch_steps(const StepsArgs &a, int grad_dtype, int pull_dtype, int blocks_per_cu,
-                        const Geometry &geo, hipStream_t s) {
+template <bool MOM, class A>
+hipError_t go_steps(const A &a, bool sync, int gdt, int pdt, unsigned lds, const Geometry &geo,
+                    hipStream_t s) {
+    if (gdt == PS_F32)
+        return pdt == PS_F32 ? go_steps_p<MOM, PS_F32, PS_F32>(a, sync, lds, geo, s)
+                             : go_steps_p<MOM, PS_F32, PS_BF16>(a, sync, lds, geo, s);
+    return pdt == PS_F32 ? go_steps_p<MOM, PS_BF16, PS_F32>(a, sync, lds, geo, s)
+                         : go_steps_p<MOM, PS_BF16, PS_BF16>(a, sync, lds, geo, s);
+}
+
+hipError_t launch_steps(const StepsArgs &a, bool sync, int grad_dtype, int pull_dtype,
+                        int blocks_per_cu, const Geometry &geo, hipStream_t s) {
     const unsigned lds =
         (blocks_per_cu >= 1 && blocks_per_cu <= 4) ? geo.lds_for_blocks[blocks_per_cu] : 0;
     if (a.k <= kCompact && a.r <= kCompact) {
@@ -854,11 +895,11 @@ hipError_t launch_steps(const StepsArgs &a, int grad_dtype, int pull_dtype, int 
         static_cast<ApplyArgsC &>(c) = compact(a);
         c.rend[0] = a.rend[0];
         c.again = a.again;
-        return c.v != nullptr ? go_steps<true>(c, grad_dtype, pull_dtype, lds, geo, s)
-                              : go_steps<false>(c, grad_dtype, pull_dtype, lds, geo, s);
+        return c.v != nullptr ? go_steps<true>(c, sync, grad_dtype, pull_dtype, lds, geo, s)
+                              : go_steps<false>(c, sync, grad_dtype, pull_dtype, lds, geo, s);
     }
-    return a.v != nullptr ? go_steps<true>(a, grad_dtype, pull_dtype, lds, geo, s)
-                          : go_steps<false>(a, grad_dtype, pull_dtype, lds, geo, s);
+    return a.v != nullptr ? go_steps<true>(a, sync, grad_dtype, pull_dtype, lds, geo, s)
+                          : go_steps<false>(a, sync, grad_dtype, pull_dtype, lds, geo, s);
 }
 
 template <int PDT, int E, bool HEAD, class P>

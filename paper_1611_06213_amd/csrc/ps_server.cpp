@@ -45,13 +45,13 @@ struct RowSet {
 // so two records compare equal byte for byte exactly when the launches are
 // the same.
 struct LaunchRecord {
-    int kind;   // 0 apply, 1 synchronous step, 2 pull fan-out, 3 steps
+    int kind;   // 0 apply, 1 synchronous step, 2 pull fan-out, 3 steps, 4 synchronous steps
     int grad_dtype;
     int pull_dtype;
     int level;
     int blocks_per_cu;
     int group;
-    gadei::StepsArgs apply;   // rend: kind 3 only
+    gadei::StepsArgs apply;   // rend: kinds 3 and 4
     gadei::PullArgs pull;
 };
 
@@ -65,6 +65,7 @@ struct StepGroup {
     int count = 0;
     int at = 0;           // the call being made
     int pushed = 0;       // pushes since the last apply call
+    bool sync = false;    // synchronous steps
     int grad_dtype = 0;
     int pull_dtype = 0;   // of the replicas, once args.r > 0
     gadei::StepsArgs args;
@@ -229,12 +230,12 @@ hipError_t run_apply(ps_server *ps, const gadei::ApplyArgs &a, int gdt, int pdt,
                 : gadei::launch_apply(a, gdt, pdt, level, shape, ps->geo, ps->stream);
 }
 
-hipError_t run_steps(ps_server *ps, const gadei::StepsArgs &a, int gdt, int pdt,
+hipError_t run_steps(ps_server *ps, const gadei::StepsArgs &a, bool sync, int gdt, int pdt,
                      int blocks_per_cu) {
     if (ps->record) {
         LaunchRecord r;
         std::memset(&r, 0, sizeof r);
-        r.kind = 3;
+        r.kind = sync ? 4 : 3;
         r.grad_dtype = gdt;
         r.pull_dtype = pdt;
         r.blocks_per_cu = blocks_per_cu;
@@ -242,7 +243,7 @@ hipError_t run_steps(ps_server *ps, const gadei::StepsArgs &a, int gdt, int pdt,
         ps->record->push_back(r);
     }
     if (ps->plan_only) return hipSuccess;
-    return gadei::launch_steps(a, gdt, pdt, blocks_per_cu, ps->geo, ps->stream);
+    return gadei::launch_steps(a, sync, gdt, pdt, blocks_per_cu, ps->geo, ps->stream);
 }
 
 hipError_t run_pull(ps_server *ps, const gadei::PullArgs &a, int dtype, int level, hipStream_t s) {
@@ -269,40 +270,52 @@ hipError_t run_pull(ps_server *ps, const gadei::PullArgs &a, int dtype, int leve
 // in cache then. Where that saves enough is steps_join's rule (ps_layout.h); a
 // single step's replicas follow fuse_replicas.
 
-int group_end(const StepGroup &g, int j) {   // replicas written up to gradient j
+int group_mark(const StepGroup &g, int j) {
     return static_cast<int>(g.args.rend[j >> 3] >> (8 * (j & 7))) & 255;
 }
 
-void set_group_end(StepGroup &g, int j, int end) {
+int group_end(const StepGroup &g, int j) {   // replicas written up to gradient j
+    return group_mark(g, j) & (gadei::kLastOfStep - 1);
+}
+
+void set_group_mark(StepGroup &g, int j, int mark) {
     uint64_t &w = g.args.rend[j >> 3];
-    w = (w & ~(uint64_t(255) << (8 * (j & 7)))) | static_cast<uint64_t>(end) << (8 * (j & 7));
+    w = (w & ~(uint64_t(255) << (8 * (j & 7)))) | static_cast<uint64_t>(mark) << (8 * (j & 7));
 }
 
 void clear_group(StepGroup &g) { std::memset(&g.args, 0, sizeof g.args); }
 
-// Enqueue the joined calls. Replicas pulled only after the last gradient (or
-// none) make an ordinary apply.
+// Enqueue the joined calls. Asynchronous ones with replicas only after the
+// last gradient (or none) make an ordinary apply, a single synchronous step
+// without replicas an ordinary one.
 int flush_group(ps_server *ps) {
     StepGroup &g = ps->group;
     if (!g.open || g.args.k == 0) return PS_OK;
     const gadei::StepsArgs a = g.args;
-    int steps = 0;   // places where replicas are written
-    for (int j = 0; j < a.k; ++j) steps += group_end(g, j) != (j > 0 ? group_end(g, j - 1) : 0);
-    const bool between = a.k > 1 && group_end(g, a.k - 2) > 0;
+    int pulls = 0, lasts = 0;   // places where replicas are written; synchronous steps
+    for (int j = 0; j < a.k; ++j) {
+        pulls += group_end(g, j) != (j > 0 ? group_end(g, j - 1) : 0);
+        lasts += (group_mark(g, j) & gadei::kLastOfStep) != 0;
+    }
+    const bool plain =
+        g.sync ? lasts == 1 && a.r == 0 : a.k == 1 || group_end(g, a.k - 2) == 0;
     clear_group(g);
     hipError_t e;
-    if (!between) {
+    if (plain) {
         gadei::ApplyArgs one = a;
         one.fronts_log2 = fronts_for(ps, one, g.grad_dtype);
-        const gadei::Shape shape = shape_for(
-            ps, gadei::apply_shape(one.k, one.v != nullptr, g.grad_dtype == PS_BF16, one.n));
-        e = run_apply(ps, one, g.grad_dtype, one.r > 0 ? g.pull_dtype : -1, 1, shape, false);
+        const bool bf16 = g.grad_dtype == PS_BF16;
+        const gadei::Shape shape =
+            shape_for(ps, g.sync ? gadei::sync_shape(one.k, one.v != nullptr, bf16)
+                                 : gadei::apply_shape(one.k, one.v != nullptr, bf16, one.n));
+        e = run_apply(ps, one, g.grad_dtype, one.r > 0 ? g.pull_dtype : -1, 1, shape, g.sync);
     } else {
         const int blocks =
             ps->force_blocks_per_cu >= 0
                 ? ps->force_blocks_per_cu
-                : gadei::steps_blocks_per_cu(a.r * elem_bytes(g.pull_dtype) / steps, a.n);
-        e = run_steps(ps, a, g.grad_dtype, g.pull_dtype, blocks);
+                : gadei::steps_blocks_per_cu(
+                      a.r * elem_bytes(g.pull_dtype) / std::max(1, pulls), a.n);
+        e = run_steps(ps, a, g.sync, g.grad_dtype, g.pull_dtype, blocks);
     }
     if (e == hipSuccess) return PS_OK;
     g.failed = true;
@@ -314,10 +327,12 @@ bool share_bytes(const void *a, size_t na, const void *b, size_t nb) {
     return x < y + nb && y < x + na;
 }
 
-bool is_apply(const ps_op &o) { return o.kind == PS_OP_APPLY || o.kind == PS_OP_APPLY_PULL; }
+bool is_apply(const ps_op &o) {
+    return o.kind == PS_OP_APPLY || o.kind == PS_OP_APPLY_PULL || o.kind == PS_OP_APPLY_SYNC;
+}
 
 // The script's calls from `from` on up to its next apply: `next` is that
-// call's index (-1: none, or other work comes first), with how many gradients
+// call's index (-1: none, or one of the other kind), with how many gradients
 // are pushed and replicas pulled before it. `same`: every such push could join
 // a group of that gradient dtype.
 struct Ahead {
@@ -336,7 +351,7 @@ Ahead look_ahead(const StepGroup &g, int from, int grad_dtype) {
         } else if (o.kind == PS_OP_PULL) {
             h.pulls += std::max(0, o.count);
         } else {
-            if (is_apply(o)) h.next = i;
+            if (is_apply(o) && (o.kind == PS_OP_APPLY_SYNC) == g.sync) h.next = i;
             break;
         }
     }
@@ -364,14 +379,14 @@ bool joining_saves(const ps_server *ps, int k, int grad_dtype, int r, int pull_d
                              ps->v != nullptr, ps->n);
 }
 
-// Add the gradients of an apply (one dtype, vector level) to the group,
+// Add the gradients of an apply or synchronous step (one dtype, vector level) to the group,
 // enqueueing what it holds first if they do not fit. A gradient that shares a
 // byte with a replica the group writes must be read after that write, so it
 // starts a new group.
-int join_gradients(ps_server *ps, const PushDesc *d, int count, int gdt) {
+int join_gradients(ps_server *ps, const PushDesc *d, int count, int gdt, bool sync) {
     StepGroup &g = ps->group;
     bool fits = g.args.k == 0 ||
-                (g.grad_dtype == gdt && g.args.k + count <= PS_MAX_QUEUE_DEPTH);
+                (g.sync == sync && g.grad_dtype == gdt && g.args.k + count <= PS_MAX_QUEUE_DEPTH);
     if (fits && g.args.r > 0) {
         const int pulls = pulls_of(g, g.at);
         fits = g.args.r + pulls <= PS_MAX_REPLICAS &&
@@ -384,6 +399,7 @@ int join_gradients(ps_server *ps, const PushDesc *d, int count, int gdt) {
     if (!fits)
         if (int rc = flush_group(ps)) return rc;
     if (g.args.k == 0) {
+        g.sync = sync;
         g.grad_dtype = gdt;
         g.args.w = ps->w;
         g.args.v = ps->v;
@@ -393,7 +409,8 @@ int join_gradients(ps_server *ps, const PushDesc *d, int count, int gdt) {
     }
     for (int i = 0; i < count; ++i) {
         g.args.g[g.args.k] = d[i].grad;
-        set_group_end(g, g.args.k, g.args.r);
+        set_group_mark(g, g.args.k,
+                       g.args.r | (sync && i == count - 1 ? gadei::kLastOfStep : 0));
         ++g.args.k;
     }
     return PS_OK;
@@ -411,7 +428,8 @@ bool join_pulls(ps_server *ps, void *const *dsts, int dtype, const std::vector<i
     if (g.args.r > 0 && g.pull_dtype != dtype) return false;
     const bool worth = ps->fuse_max_r >= 0
                            ? r <= ps->fuse_max_r
-                           : g.args.r > 0 || gadei::fuse_replicas(r, g.args.k, ps->n) ||
+                           : g.args.r > 0 ||
+                                 (!g.sync && gadei::fuse_replicas(r, g.args.k, ps->n)) ||
                                  (joining_saves(ps, g.args.k, g.grad_dtype, r, dtype) &&
                                   next_step_joins(g, r));
     if (!worth) return false;
@@ -436,7 +454,8 @@ bool join_pulls(ps_server *ps, void *const *dsts, int dtype, const std::vector<i
             }
         g.args.dst[g.args.r++] = dsts[i];
     }
-    set_group_end(g, g.args.k - 1, g.args.r);
+    set_group_mark(g, g.args.k - 1,
+                   g.args.r | (g.sync ? gadei::kLastOfStep : 0));
     return true;
 }
 
@@ -467,7 +486,7 @@ int launch_batch(ps_server *ps, const std::vector<PushDesc> &items, int pull_dty
             ++end;
         }
         if (ps->group.open && level == 1) {
-            if (int rc = join_gradients(ps, &items[start], static_cast<int>(end - start), gdt))
+            if (int rc = join_gradients(ps, &items[start], static_cast<int>(end - start), gdt, false))
                 return rc;
             start = end;
             continue;
@@ -638,8 +657,8 @@ hipError_t launch_plan(ps_server *ps, const std::vector<LaunchRecord> &plan) {
                 break;
             case 2: e = gadei::launch_pull(r.pull, r.pull_dtype, r.level, ps->geo, ps->stream); break;
             default:
-                e = gadei::launch_steps(r.apply, r.grad_dtype, r.pull_dtype, r.blocks_per_cu,
-                                        ps->geo, ps->stream);
+                e = gadei::launch_steps(r.apply, r.kind == 4, r.grad_dtype, r.pull_dtype,
+                                        r.blocks_per_cu, ps->geo, ps->stream);
         }
     }
     return e;
@@ -892,6 +911,15 @@ int ps_apply_sync(ps_server *ps) {
     if (int rc = ps->proto.plan_sync(b)) return rc;
     const int gdt = b.items.front().dtype;
     if (int rc = use_device(ps)) return rc;
+    if (ps->group.open &&
+        std::all_of(b.items.begin(), b.items.end(), [](const PushDesc &d) {
+            return d.ready == nullptr && grad_level(d.grad) == 1;
+        })) {
+        if (int rc = join_gradients(ps, b.items.data(), static_cast<int>(b.items.size()), gdt, true))
+            return rc;
+        ps->proto.commit_sync(b);
+        return PS_OK;
+    }
     if (int rc = flush_group(ps)) return rc;
     if (int rc = wait_ready(ps, b.items)) return rc;
     gadei::ApplyArgs a;

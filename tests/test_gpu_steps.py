@@ -122,7 +122,7 @@ def compare(torch, n, m, ops, size, depth=64, seed=0, fusion=None, graph=False):
     srv.close()
 
 
-def regular(n, steps, k, r, learners, gdt, pdt, fused, align=8):
+def regular(n, steps, k, r, learners, gdt, pdt, fused, align=8, apply="apply"):
     """steps x (k pushes, an apply, r pulls), buffers `align` 16-bit units apart
     from each other's ends."""
     def room(dt):
@@ -137,7 +137,7 @@ def regular(n, steps, k, r, learners, gdt, pdt, fused, align=8):
         if fused:
             ops.append(("apply_pull", dsts, pdt))
         else:
-            ops.append(("apply",))
+            ops.append((apply,))
             if dsts:
                 ops.append(("pull", dsts, pdt))
     return ops, at + learners * room(pdt)
@@ -160,6 +160,22 @@ def test_steps(torch, n, k, r, learners, steps):
         i += 1
         ops, size = regular(n, steps, k, r, learners, gdt, pdt, fused=i % 2 == 0)
         compare(torch, n, 0.9 if i < 3 else 0.0, ops, size, seed=n + i, graph=i == 2)
+
+
+@pytest.mark.parametrize("n", [1, 9, 4099])
+@pytest.mark.parametrize("k,r,learners,steps", [
+    (1, 1, 4, 5), (3, 2, 2, 3), (4, 4, 4, 2), (7, 0, 1, 4), (8, 1, 1, 1), (5, 3, 7, 9),
+    (17, 2, 5, 3), (32, 32, 32, 2), (40, 2, 2, 2), (16, 5, 5, 8)])
+def test_synchronous_steps(torch, n, k, r, learners, steps):
+    """Averaged steps in one launch; a step's gradients lie across load groups."""
+    i = 0
+    for gdt, pdt in ((F32, F32), (BF16, BF16), (F32, BF16), (BF16, F32)):
+        i += 1
+        ops, size = regular(n, steps, k, r, learners, gdt, pdt, fused=False, apply="sync")
+        compare(torch, n, 0.9 if i % 2 else 0.0, ops, size, seed=n + i, graph=i == 1)
+        if i == 1:   # both kinds of step in one script
+            mixed = ops + [("apply",) if o[0] == "sync" else o for o in ops] + ops
+            compare(torch, n, 0.9, mixed, size, seed=n)
 
 
 @pytest.mark.parametrize("align", [1, 2, 4])
