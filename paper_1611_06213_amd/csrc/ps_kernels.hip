@@ -2,9 +2,9 @@
 //
 // The kernels are pure streams over HBM: every byte is read or written once
 // per launch and there is no reuse to stage in LDS and no contraction for
-// the matrix cores. What matters is that each lane moves whole, aligned
-// 16-byte chunks (4 fp32 or 8 bf16 values; narrower only for misaligned
-// buffers), that enough loads are in flight, that nothing is re-read, and
+// the matrix cores. What matters is that each lane moves whole 16-byte
+// chunks (4 fp32 or 8 bf16 values; single values only for bf16 gradients on
+// odd 2-byte boundaries), that enough loads are in flight, that nothing is re-read, and
 // which coordinates the resident blocks work on at the same time (the DRAM
 // serves some access patterns faster than others: see front_block,
 // pull_tiled and pull_slices).
