@@ -983,8 +983,18 @@ int ps_apply_pull(ps_server *ps, int n, const int *learner_ids, void *const *dst
     const int r = static_cast<int>(write.size());
     const bool fuse = ps->fuse_max_r >= 0 ? r <= ps->fuse_max_r
                                            : gadei::fuse_replicas(r, static_cast<int>(b.items.size()), ps->n);
-    if (fuse && !ps->group.open) {
-        if (int rc = launch_batch(ps, b.items, dst_dtype, dsts, write)) return rc;
+    // Gradients for the scalar kernels join no group: in a script too, their
+    // replicas are written by the same rule as outside one.
+    const bool joins = ps->group.open &&
+                       std::all_of(b.items.begin(), b.items.end(),
+                                   [](const PushDesc &d) { return grad_level(d.grad) == 1; });
+    if (fuse && !joins) {
+        const bool open = ps->group.open;
+        if (int rc = flush_group(ps)) return rc;
+        ps->group.open = false;
+        const int rc = launch_batch(ps, b.items, dst_dtype, dsts, write);
+        ps->group.open = open;
+        if (rc) return rc;
     } else {
         static const std::vector<int> none;
         if (int rc = launch_batch(ps, b.items, -1, nullptr, none)) return rc;
@@ -1294,7 +1304,12 @@ int ps_run(ps_server *ps, const ps_op *ops, int count, int *done) {
     }
     // The calls before a refused one are done: they go out now. (fail() is not
     // called on success, so the refusal's message stays.)
-    if (int rc2 = flush_group(ps)) rc = rc2;
+    try {
+        if (int rc2 = flush_group(ps)) rc = rc2;
+    } catch (...) {   // a plan being recorded could not grow: nothing was enqueued
+        rc = fail(PS_ENOMEM, "host allocation failed");
+        g.failed = true;
+    }
     g.open = false;
     if (done) *done = g.failed ? enqueued : completed;
     return rc;

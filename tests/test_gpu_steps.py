@@ -188,6 +188,18 @@ def test_steps_element_aligned(torch, align):
         compare(torch, 4099, 0.9, ops, size, seed=align)
 
 
+@pytest.mark.parametrize("k,r", [(1, 1), (5, 3), (16, 9)])
+def test_steps_of_odd_bf16_gradients(torch, k, r):
+    """Rows an odd number of bf16 values apart: steps whose gradients all lie
+    on 4-byte boundaries join, the others keep the scalar kernels and write
+    their replicas from the apply or by the fan-out."""
+    for pdt in (F32, BF16):
+        ops, size = regular(4098, 4, k, r, 16, BF16, pdt, fused=True, align=1 if pdt == BF16 else 2)
+        ops = [(o[0], o[1], o[2] + (pdt == F32 and i % 2), o[3]) if o[0] == "push" else o
+               for i, o in enumerate(ops)]
+        compare(torch, 4098, 0.9, ops, size, seed=k, graph=True)
+
+
 @pytest.mark.parametrize("fusion", [0, 1, 64])
 def test_steps_with_a_fusion_limit(torch, fusion):
     ops, size = regular(5003, 5, 2, 2, 4, F32, F32, fused=True)
