@@ -1,0 +1,86 @@
+"""The server's host code on the CPU (tests/host_server.py): how the calls of a
+script go out, what a failed launch leaves behind, and that joined and single
+calls do the same."""
+import random
+
+import numpy as np
+import pytest
+
+from paper_1611_06213_amd import ps
+from tests import host_server as hs
+
+F32, BF16 = ps.PS_F32, ps.PS_BF16
+HEADLINE, LARGE = 138_357_544, 200_000_000   # parameters of VGG-16 and of the bf16 workload
+
+
+@pytest.fixture(scope="module")
+def built(tmp_path_factory):
+    return hs.build(str(tmp_path_factory.mktemp("host") / "libhost.so"))
+
+
+@pytest.fixture
+def lib(built, monkeypatch):
+    monkeypatch.setattr(ps, "_lib", built)
+    return built
+
+
+class Memory:
+    """`places` buffers of n values, each of room for fp32, in one array of
+    2-byte units with finite values of either type."""
+
+    def __init__(self, n, places, seed=0):
+        self.step = 2 * n + 6
+        vals = np.random.default_rng(seed).normal(0, 1e-2, places * self.step // 2 + 1)
+        self.a = vals.astype(np.float32).view(np.uint16).copy()
+        self.a[(self.a & 0x7F80) == 0x7F80] = 0x3C00
+        self.base = self.a.ctypes.data
+
+    def __getitem__(self, i):
+        return i * self.step
+
+
+def one_by_one(srv, ops, base):
+    """The script's calls, each by itself: (status, calls made)."""
+    for i, op in enumerate(ops):
+        rc, _ = ps.ps_run(srv.h, hs.script([op], base))
+        if rc != ps.PS_OK:
+            return rc, i
+    return ps.PS_OK, len(ops)
+
+
+@pytest.mark.parametrize("seed", range(40))
+def test_joined_calls_equal_single_ones(lib, seed):
+    """Random scripts over buffers of one memory, refused calls among them: the
+    same weights, memory, state, status and number of calls."""
+    r = random.Random(seed)
+    n, m = r.choice([1, 5, 33]), r.choice([0.0, 0.9])
+    mode, skip = r.choice([ps.PS_QUEUE_FIFO, ps.PS_QUEUE_ROUND_ROBIN]), r.random() < 0.5
+    depth = r.choice([4, 16])
+    gdts = r.choice([[F32], [BF16], [F32, F32, BF16]])
+    pdts = r.choice([[F32], [BF16], [F32, BF16]])
+    mems = [Memory(n, 14, seed), Memory(n, 14, seed)]
+    ops = []
+    for _ in range(120):
+        kind = r.choice(["push"] * 5 + ["apply", "apply", "sync", "pull", "pull", "apply_pull"])
+        if kind == "push":   # (an odd place of bf16 gradients lies on no 4-byte boundary)
+            dt = r.choice(gdts)
+            ops.append((kind, r.randrange(3), mems[0][r.randrange(8)] + (r.random() < 0.1 and dt == BF16), dt))
+        elif kind in ("apply", "sync"):
+            ops.append((kind,))
+        else:
+            ops.append((kind, r.sample([mems[0][8 + i] for i in range(6)], r.randrange(4)), r.choice(pdts)))
+    got = []
+    for mem, run in zip(mems, (None, one_by_one)):
+        srv = hs.Host(lib, n, momentum=m, depth=depth, skip=skip)
+        if mode:
+            assert ps.ps_set_queue_mode(srv.h, mode, 3) == 0
+        at, log = 0, []
+        while at < len(ops):   # a refused call is left out, the rest goes on
+            rc, done = (run(srv, ops[at:], mem.base) if run
+                        else ps.ps_run(srv.h, hs.script(ops[at:], mem.base)))
+            log.append((rc, done))
+            at += done + 1
+        v = srv.v()
+        got.append((log, srv.state(), srv.w().tobytes(), b"" if v is None else v.tobytes(), mem.a.tobytes()))
+        srv.close()
+    assert got[0] == got[1]
