@@ -66,8 +66,8 @@ struct StepGroup {
     int at = 0;           // the call being made
     int pushed = 0;       // pushes since the last apply call
     bool sync = false;    // synchronous steps
-    int grad_dtype = 0;
-    int pull_dtype = 0;   // of the replicas, once args.r > 0
+    int grad_dtype = PS_F32;
+    int pull_dtype = PS_F32;   // of the replicas, once args.r > 0
     gadei::StepsArgs args;
 };
 
@@ -283,7 +283,13 @@ void set_group_mark(StepGroup &g, int j, int mark) {
     w = (w & ~(uint64_t(255) << (8 * (j & 7)))) | static_cast<uint64_t>(mark) << (8 * (j & 7));
 }
 
-void clear_group(StepGroup &g) { std::memset(&g.args, 0, sizeof g.args); }
+// Empty the group: nothing of it stays for the next one (a recorded launch
+// holds every field).
+void clear_group(StepGroup &g) {
+    std::memset(&g.args, 0, sizeof g.args);
+    g.sync = false;
+    g.grad_dtype = g.pull_dtype = PS_F32;
+}
 
 // Enqueue the joined calls. Asynchronous ones with replicas only after the
 // last gradient (or none) make an ordinary apply, a single synchronous step
@@ -292,30 +298,31 @@ int flush_group(ps_server *ps) {
     StepGroup &g = ps->group;
     if (!g.open || g.args.k == 0) return PS_OK;
     const gadei::StepsArgs a = g.args;
+    const bool sync = g.sync;
+    const int gdt = g.grad_dtype, pdt = g.pull_dtype;
     int pulls = 0, lasts = 0;   // places where replicas are written; synchronous steps
     for (int j = 0; j < a.k; ++j) {
         pulls += group_end(g, j) != (j > 0 ? group_end(g, j - 1) : 0);
         lasts += (group_mark(g, j) & gadei::kLastOfStep) != 0;
     }
     const bool plain =
-        g.sync ? lasts == 1 && a.r == 0 : a.k == 1 || group_end(g, a.k - 2) == 0;
+        sync ? lasts == 1 && a.r == 0 : a.k == 1 || group_end(g, a.k - 2) == 0;
     clear_group(g);
     hipError_t e;
     if (plain) {
         gadei::ApplyArgs one = a;
-        one.fronts_log2 = fronts_for(ps, one, g.grad_dtype);
-        const bool bf16 = g.grad_dtype == PS_BF16;
+        one.fronts_log2 = fronts_for(ps, one, gdt);
+        const bool bf16 = gdt == PS_BF16;
         const gadei::Shape shape =
-            shape_for(ps, g.sync ? gadei::sync_shape(one.k, one.v != nullptr, bf16)
-                                 : gadei::apply_shape(one.k, one.v != nullptr, bf16, one.n));
-        e = run_apply(ps, one, g.grad_dtype, one.r > 0 ? g.pull_dtype : -1, 1, shape, g.sync);
+            shape_for(ps, sync ? gadei::sync_shape(one.k, one.v != nullptr, bf16)
+                               : gadei::apply_shape(one.k, one.v != nullptr, bf16, one.n));
+        e = run_apply(ps, one, gdt, one.r > 0 ? pdt : -1, 1, shape, sync);
     } else {
         const int blocks =
             ps->force_blocks_per_cu >= 0
                 ? ps->force_blocks_per_cu
-                : gadei::steps_blocks_per_cu(
-                      a.r * elem_bytes(g.pull_dtype) / std::max(1, pulls), a.n);
-        e = run_steps(ps, a, g.sync, g.grad_dtype, g.pull_dtype, blocks);
+                : gadei::steps_blocks_per_cu(a.r * elem_bytes(pdt) / std::max(1, pulls), a.n);
+        e = run_steps(ps, a, sync, gdt, pdt, blocks);
     }
     if (e == hipSuccess) return PS_OK;
     g.failed = true;

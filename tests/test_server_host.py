@@ -84,3 +84,25 @@ def test_joined_calls_equal_single_ones(lib, seed):
         got.append((log, srv.state(), srv.w().tobytes(), b"" if v is None else v.tobytes(), mem.a.tobytes()))
         srv.close()
     assert got[0] == got[1]
+
+
+def pushes(mem, count, dt=F32, at=0):
+    return [("push", j % 3, mem[at + j], dt) for j in range(count)]
+
+
+def test_a_plan_does_not_depend_on_earlier_replicas(lib):
+    """Joined synchronous steps without replicas are the same launch whatever
+    type of replica was pulled before."""
+    mem = Memory(9, 8)
+    sync = pushes(mem, 1) + [("sync",)] + pushes(mem, 1, at=1) + [("sync",)]
+    pull16 = pushes(mem, 1) + [("apply_pull", [mem[6]], BF16)]
+    srv = hs.Host(lib, 9)
+    for ops in (sync, sync + pull16):
+        s = hs.script(ops, mem.base)
+        rc, g = ps.ps_graph_create(srv.h, s)
+        assert rc == 0
+        for _ in range(2):
+            assert ps.ps_graph_launch(srv.h, g) == 0, ps.ps_last_error()
+            assert ps.ps_run(srv.h, hs.script(pull16, mem.base))[0] == 0
+        ps.ps_graph_destroy(g)
+    srv.close()
