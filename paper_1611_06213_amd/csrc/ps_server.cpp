@@ -64,6 +64,7 @@ struct StepGroup {
     const ps_op *ops = nullptr;   // the script, for a look at the step ahead
     int count = 0;
     int at = 0;           // the call being made
+    int first = 0;        // the call whose gradients opened the group
     int pushed = 0;       // pushes since the last apply call
     bool sync = false;    // synchronous steps
     int grad_dtype = PS_F32;
@@ -406,6 +407,7 @@ int join_gradients(ps_server *ps, const PushDesc *d, int count, int gdt, bool sy
     if (!fits)
         if (int rc = flush_group(ps)) return rc;
     if (g.args.k == 0) {
+        g.first = g.at;
         g.sync = sync;
         g.grad_dtype = gdt;
         g.args.w = ps->w;
@@ -1296,11 +1298,10 @@ int ps_run(ps_server *ps, const ps_op *ops, int count, int *done) {
     g.count = count;
     g.pushed = 0;
     clear_group(g);
-    int rc = PS_OK, completed = 0, enqueued = 0;   // calls; those whose device work is enqueued
+    int rc = PS_OK, completed = 0;
     try {
         for (; completed < count; ++completed) {
             const ps_op &o = ops[completed];
-            if (g.args.k == 0) enqueued = completed;
             if (o.kind == PS_OP_PUSH) ++g.pushed;
             else if (is_apply(o)) g.pushed = 0;
             g.at = completed;
@@ -1318,7 +1319,7 @@ int ps_run(ps_server *ps, const ps_op *ops, int count, int *done) {
         g.failed = true;
     }
     g.open = false;
-    if (done) *done = g.failed ? enqueued : completed;
+    if (done) *done = g.failed ? g.first : completed;
     return rc;
 }
 

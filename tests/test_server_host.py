@@ -106,3 +106,15 @@ def test_a_plan_does_not_depend_on_earlier_replicas(lib):
             assert ps.ps_run(srv.h, hs.script(pull16, mem.base))[0] == 0
         ps.ps_graph_destroy(g)
     srv.close()
+
+
+@pytest.mark.parametrize("fail,done", [(0, 1), (1, 129), (2, 257)])
+def test_done_names_the_calls_before_a_failed_launch(lib, fail, done):
+    """300 calls go out in launches of 64 gradients: `done` counts the calls
+    before those of the launch that failed, not those of the first one."""
+    mem = Memory(3, 1)
+    srv = hs.Host(lib, 3)
+    srv.clear(fail)
+    assert ps.ps_run(srv.h, hs.script([*pushes(mem, 1), ("apply",)] * 150, mem.base)) == (ps.PS_EHIP, done)
+    assert [(l.kind, l.k) for l in srv.launches()] == [(hs.APPLY, 64)] * fail
+    srv.close()
