@@ -405,7 +405,8 @@ typedef struct ps_op {
  * them may go out as one kernel launch (up to PS_MAX_QUEUE_DEPTH gradients and PS_MAX_REPLICAS replicas),
  * with the same results; every kernel has been enqueued when ps_run returns.
  * If such a launch fails (PS_EHIP), *done counts the calls before the ones
- * that went out in it.
+ * that went out in it, and the server's state is as those calls left it: the
+ * gradients pushed later are not queued, no replica pulled later is current.
  * PS_EINVAL for an unknown kind or ops == NULL with count > 0. */
 int ps_run(ps_server *ps, const ps_op *ops, int count, int *done);
 

@@ -49,6 +49,7 @@ int Protocol::push(int learner, int dtype, const void *grad, void *ready) {
     const uint64_t lts =
         static_cast<size_t>(learner) < learner_ts.size() ? learner_ts[learner] : 0;
     const PushDesc d{learner, dtype, grad, lts, ready};
+    if (journal_) journal_->room(1);
     if (mode == PS_QUEUE_FIFO) {
         if (static_cast<int>(fifo_.size()) >= depth) {
             stats.pushes_rejected += 1;
@@ -67,6 +68,7 @@ int Protocol::push(int learner, int dtype, const void *grad, void *ready) {
         rr_count_ += 1;
     }
     stats.pushes_accepted += 1;
+    if (journal_) journal_->entries.push_back({Journal::Entry::kPushed, learner, d, 0, {}});
     return PS_OK;
 }
 
@@ -130,6 +132,9 @@ int Protocol::plan_sync(Batch &b) const {
 }
 
 void Protocol::consume(const Batch &b) {
+    if (journal_)
+        for (const PushDesc &d : b.items)
+            journal_->entries.push_back({Journal::Entry::kTaken, d.learner, d, 0, {}});
     if (mode == PS_QUEUE_FIFO) {
         fifo_.erase(fifo_.begin(), fifo_.begin() + static_cast<ptrdiff_t>(b.items.size()));
         return;
@@ -217,8 +222,12 @@ void Protocol::commit_pulls(int n, const int *ids, void *const *dsts, int dtype,
                             const std::vector<int> &write, bool ordered) {
     stats.pulls += static_cast<uint64_t>(n);
     stats.pulls_skipped += static_cast<uint64_t>(n) - write.size();
+    if (journal_) journal_->room(static_cast<size_t>(n));
     for (int i = 0; i < n; ++i) {
         grow(ids[i]);
+        if (journal_)
+            journal_->entries.push_back({Journal::Entry::kPulled, ids[i], {}, learner_ts[ids[i]],
+                                         last_pull[ids[i]]});
         learner_ts[ids[i]] = ts;
     }
     for (int i : write) {
@@ -228,6 +237,57 @@ void Protocol::commit_pulls(int n, const int *ids, void *const *dsts, int dtype,
         k.ts = ts;
         k.valid = ordered;
     }
+}
+
+void Journal::room(size_t count) {
+    const size_t need = entries.size() + count;
+    if (need > entries.capacity()) entries.reserve(std::max(need, 2 * entries.capacity()));
+}
+
+void Protocol::mark(Journal &j) {
+    j.entries.clear();
+    j.ts = ts;
+    j.last_served = last_served;
+    j.learners = learner_ts.size();
+    j.stats = stats;
+    j.last_staleness = last_staleness;
+    j.last_applied = last_applied;
+    journal_ = &j;
+}
+
+void Protocol::forget() { journal_ = nullptr; }
+
+void Protocol::undo() {
+    if (journal_ == nullptr) return;
+    Journal &j = *journal_;
+    journal_ = nullptr;
+    for (auto e = j.entries.rbegin(); e != j.entries.rend(); ++e) {
+        if (e->kind == Journal::Entry::kPulled) {
+            learner_ts[e->learner] = e->learner_ts;
+            last_pull[e->learner] = e->pull;
+        } else if (mode == PS_QUEUE_FIFO) {
+            if (e->kind == Journal::Entry::kPushed) fifo_.pop_back();
+            else fifo_.insert(fifo_.begin(), e->item);
+        } else {
+            auto &q = rr_[e->learner];
+            if (e->kind == Journal::Entry::kPushed) {
+                q.pop_back();
+                rr_count_ -= 1;
+                if (q.empty()) waiting_.erase(e->learner);
+            } else {
+                q.push_front(e->item);
+                rr_count_ += 1;
+                waiting_.insert(e->learner);
+            }
+        }
+    }
+    learner_ts.resize(j.learners);
+    last_pull.resize(j.learners);
+    ts = j.ts;
+    last_served = j.last_served;
+    stats = j.stats;
+    last_staleness = j.last_staleness;
+    last_applied = j.last_applied;
 }
 
 bool Protocol::references(const void *lo, const void *hi) const {

@@ -13,7 +13,10 @@
 //
 // Every operation that can fail validates first and changes nothing on
 // failure; the plan_* / commit_* split lets the caller launch device work
-// between the two and commit only what it launched.
+// between the two and commit only what it launched. Where several calls go out
+// in one launch, the later ones are planned on the state that the earlier ones
+// leave, so they are committed before it: a Journal then takes back what was
+// committed if the launch fails.
 #pragma once
 
 #include <stddef.h>
@@ -56,6 +59,28 @@ struct Batch {
     std::vector<PushDesc> items;
     std::vector<std::pair<int, int>> taken;   // (learner, count), round robin
     int last_served = -1;
+};
+
+// What Protocol::undo needs to put the state back to Protocol::mark: the
+// scalars as they were, and each push, queue removal and pull since.
+struct Journal {
+    struct Entry {
+        enum Kind { kPushed, kTaken, kPulled } kind;
+        int learner;
+        PushDesc item;         // kTaken
+        uint64_t learner_ts;   // kPulled: the learner's before the pull
+        PullKey pull;
+    };
+    std::vector<Entry> entries;
+    uint64_t ts = 0;
+    int last_served = -1;
+    size_t learners = 0;
+    ps_stats stats{};
+    std::vector<int64_t> last_staleness;
+    std::vector<int> last_applied;
+
+    // Make room for `count` more entries.
+    void room(size_t count);
 };
 
 struct Protocol {
@@ -109,6 +134,12 @@ struct Protocol {
     void commit_pulls(int n, const int *ids, void *const *dsts, int dtype,
                       const std::vector<int> &write, bool ordered);
 
+    // From mark(j) on, pushes, commits and empty applies can be taken back by
+    // undo(), until forget(). All three end an earlier mark.
+    void mark(Journal &j);
+    void undo();
+    void forget();
+
     // Whether a queued gradient starts in [lo, hi).
     bool references(const void *lo, const void *hi) const;
 
@@ -130,6 +161,7 @@ struct Protocol {
     void restore(uint64_t new_ts, int new_last_served, const std::vector<uint64_t> &lts);
 
    private:
+    Journal *journal_ = nullptr;             // marked
     std::vector<PushDesc> fifo_;             // FIFO mode
     std::vector<std::deque<PushDesc>> rr_;   // round robin: queue of each learner id
     std::set<int> waiting_;                  // ... ids whose queue is not empty

@@ -70,6 +70,7 @@ struct StepGroup {
     int grad_dtype = PS_F32;
     int pull_dtype = PS_F32;   // of the replicas, once args.r > 0
     gadei::StepsArgs args;
+    gadei::Journal journal;   // of the calls from `first` on
 };
 
 struct ps_server {
@@ -294,7 +295,8 @@ void clear_group(StepGroup &g) {
 
 // Enqueue the joined calls. Asynchronous ones with replicas only after the
 // last gradient (or none) make an ordinary apply, a single synchronous step
-// without replicas an ordinary one.
+// without replicas an ordinary one. If the launch fails, those calls are not
+// made: the protocol is as the one before g.first left it.
 int flush_group(ps_server *ps) {
     StepGroup &g = ps->group;
     if (!g.open || g.args.k == 0) return PS_OK;
@@ -325,8 +327,12 @@ int flush_group(ps_server *ps) {
                 : gadei::steps_blocks_per_cu(a.r * elem_bytes(pdt) / std::max(1, pulls), a.n);
         e = run_steps(ps, a, sync, gdt, pdt, blocks);
     }
-    if (e == hipSuccess) return PS_OK;
+    if (e == hipSuccess) {
+        ps->proto.forget();
+        return PS_OK;
+    }
     g.failed = true;
+    ps->proto.undo();
     return fail_hip(e, "apply kernel launch");
 }
 
@@ -407,6 +413,7 @@ int join_gradients(ps_server *ps, const PushDesc *d, int count, int gdt, bool sy
     if (!fits)
         if (int rc = flush_group(ps)) return rc;
     if (g.args.k == 0) {
+        ps->proto.mark(g.journal);
         g.first = g.at;
         g.sync = sync;
         g.grad_dtype = gdt;
@@ -1008,7 +1015,9 @@ int ps_apply_pull(ps_server *ps, int n, const int *learner_ids, void *const *dst
         static const std::vector<int> none;
         if (int rc = launch_batch(ps, b.items, -1, nullptr, none)) return rc;
         if (int rc = launch_pulls(ps, dsts, dst_dtype, write, true)) {
-            ps->proto.commit_async(b);   // the apply is on the stream: its gradients are consumed
+            // the apply is on the stream, its gradients are consumed, unless
+            // it was the launch of the joined calls that failed
+            if (!ps->group.failed) ps->proto.commit_async(b);
             return rc;
         }
     }
@@ -1318,8 +1327,9 @@ int ps_run(ps_server *ps, const ps_op *ops, int count, int *done) {
         rc = fail(PS_ENOMEM, "host allocation failed");
         g.failed = true;
     }
-    g.open = false;
     if (done) *done = g.failed ? g.first : completed;
+    g.open = g.failed = false;
+    ps->proto.forget();
     return rc;
 }
 

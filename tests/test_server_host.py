@@ -118,3 +118,54 @@ def test_done_names_the_calls_before_a_failed_launch(lib, fail, done):
     assert ps.ps_run(srv.h, hs.script([*pushes(mem, 1), ("apply",)] * 150, mem.base)) == (ps.PS_EHIP, done)
     assert [(l.kind, l.k) for l in srv.launches()] == [(hs.APPLY, 64)] * fail
     srv.close()
+
+
+def fail_script(mem):
+    """Steps of either kind, replicas of two types, gradients of two: several
+    joined launches and single ones."""
+    ops = []
+    for s in range(3):
+        ops += pushes(mem, 2) + [("apply_pull", [mem[8], mem[9]], F32)]
+        ops += pushes(mem, 1) + [("apply",), ("pull", [mem[8]], F32), ("pull", [mem[10]], BF16)]
+        ops += pushes(mem, 3) + [("sync",)] + pushes(mem, 2, at=2) + [("sync",), ("pull", [mem[11]], F32)]
+        ops += pushes(mem, 2, BF16, at=5) + [("apply",)] + pushes(mem, 1, at=3)   # one stays queued
+    return ops
+
+
+@pytest.mark.parametrize("mode", [ps.PS_QUEUE_FIFO, ps.PS_QUEUE_ROUND_ROBIN])
+@pytest.mark.parametrize("skip", [True, False])
+def test_after_a_failed_launch_only_the_calls_before_it_are_made(lib, mode, skip):
+    """Whichever launch of a script fails: `done` calls are made, the server
+    says and holds what those calls alone leave, and the script goes on from there
+    to the same end."""
+    def server(mem):
+        srv = hs.Host(lib, 9, momentum=0.9, depth=8, skip=skip)
+        if mode:
+            assert ps.ps_set_queue_mode(srv.h, mode, 8) == 0
+        return srv
+
+    def all_of(srv, mem):
+        return srv.state(), srv.w().tobytes(), srv.v().tobytes(), mem.a.tobytes()
+
+    whole = Memory(9, 14)
+    ops = fail_script(whole)
+    srv = server(whole)
+    srv.clear()
+    assert ps.ps_run(srv.h, hs.script(ops, whole.base)) == (ps.PS_OK, len(ops))
+    launches, end = len(srv.launches()), all_of(srv, whole)
+    srv.close()
+    assert launches > 8
+    for fail in range(launches):
+        mem, ref = Memory(9, 14), Memory(9, 14)
+        a = server(mem)
+        a.clear(fail)
+        rc, done = ps.ps_run(a.h, hs.script(ops, mem.base))
+        assert rc == ps.PS_EHIP and done < len(ops)
+        got = all_of(a, mem)
+        b = server(ref)
+        assert one_by_one(b, ops[:done], ref.base) == (ps.PS_OK, done)
+        assert got == all_of(b, ref), (fail, done)
+        b.close()
+        assert ps.ps_run(a.h, hs.script(ops[done:], mem.base)) == (ps.PS_OK, len(ops) - done)
+        assert all_of(a, mem) == end, (fail, done)
+        a.close()
