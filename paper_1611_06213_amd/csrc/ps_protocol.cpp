@@ -30,14 +30,18 @@ int check_learner(int id) {
     return PS_OK;
 }
 
-Protocol::Protocol() { fifo_.reserve(PS_MAX_QUEUE_DEPTH); }
+Protocol::Protocol() {
+    fifo_.reserve(PS_MAX_QUEUE_DEPTH);
+    last_staleness.reserve(PS_MAX_QUEUE_DEPTH);
+    last_applied.reserve(PS_MAX_QUEUE_DEPTH);
+}
 
 size_t Protocol::pending() const { return mode == PS_QUEUE_FIFO ? fifo_.size() : rr_count_; }
 
 void Protocol::grow(int id) {
     if (static_cast<size_t>(id) >= learner_ts.size()) {
-        learner_ts.resize(static_cast<size_t>(id) + 1, 0);
         last_pull.resize(static_cast<size_t>(id) + 1);
+        learner_ts.resize(static_cast<size_t>(id) + 1, 0);
     }
 }
 
@@ -63,8 +67,13 @@ int Protocol::push(int learner, int dtype, const void *grad, void *ready) {
             stats.pushes_rejected += 1;
             return fail(PS_EFULL, "learner %d queue full (%d slots)", learner, slots);
         }
-        q.push_back(d);
-        waiting_.insert(learner);
+        const bool waits = !waiting_.insert(learner).second;
+        try {
+            q.push_back(d);
+        } catch (...) {
+            if (!waits) waiting_.erase(learner);
+            throw;
+        }
         rr_count_ += 1;
     }
     stats.pushes_accepted += 1;
@@ -218,11 +227,15 @@ int Protocol::plan_pulls(int n, const int *ids, void *const *dsts, int dtype, ui
     return PS_OK;
 }
 
+void Protocol::prepare_pulls(int n, const int *ids) {
+    if (journal_) journal_->room(static_cast<size_t>(n));
+    for (int i = 0; i < n; ++i) grow(ids[i]);
+}
+
 void Protocol::commit_pulls(int n, const int *ids, void *const *dsts, int dtype,
                             const std::vector<int> &write, bool ordered) {
     stats.pulls += static_cast<uint64_t>(n);
     stats.pulls_skipped += static_cast<uint64_t>(n) - write.size();
-    if (journal_) journal_->room(static_cast<size_t>(n));
     for (int i = 0; i < n; ++i) {
         grow(ids[i]);
         if (journal_)

@@ -127,6 +127,9 @@ struct Protocol {
     // pulls may not share a buffer.
     int plan_pulls(int n, const int *ids, void *const *dsts, int dtype, uint64_t ts_after,
                    std::vector<int> &write) const;
+    // Make room for the commit of these (valid) pulls, which then cannot throw:
+    // to be called before their launch.
+    void prepare_pulls(int n, const int *ids);
     // `ordered`: the replicas were written after every earlier apply, so
     // they hold the weights at the current timestamp and a repeat can be
     // skipped. A lock-free pull may have raced an apply: its replicas never

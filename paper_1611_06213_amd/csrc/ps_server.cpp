@@ -396,9 +396,12 @@ bool joining_saves(const ps_server *ps, int k, int grad_dtype, int r, int pull_d
 // Add the gradients of an apply or synchronous step (one dtype, vector level) to the group,
 // enqueueing what it holds first if they do not fit. A gradient that shares a
 // byte with a replica the group writes must be read after that write, so it
-// starts a new group.
+// starts a new group. Nothing the call does after this can throw: its commit
+// finds its room (a call that throws is not made, and its gradients must not be in
+// the group).
 int join_gradients(ps_server *ps, const PushDesc *d, int count, int gdt, bool sync) {
     StepGroup &g = ps->group;
+    g.journal.room(PS_MAX_QUEUE_DEPTH + PS_MAX_REPLICAS);
     bool fits = g.args.k == 0 ||
                 (g.sync == sync && g.grad_dtype == gdt && g.args.k + count <= PS_MAX_QUEUE_DEPTH);
     if (fits && g.args.r > 0) {
@@ -966,6 +969,7 @@ int ps_pull_many(ps_server *ps, int n, const int *learner_ids, void *const *dsts
     if (int rc = ps->proto.plan_pulls(n, learner_ids, dsts, dst_dtype, ps->proto.ts, write))
         return rc;
     if (int rc = check_dsts(ps, n, dsts, dst_dtype)) return rc;
+    ps->proto.prepare_pulls(n, learner_ids);
     if (!write.empty()) {
         if (int rc = use_device(ps)) return rc;
         if (int rc = launch_pulls(ps, dsts, dst_dtype, write, false)) return rc;
@@ -993,6 +997,7 @@ int ps_apply_pull(ps_server *ps, int n, const int *learner_ids, void *const *dst
     if (int rc = ps->proto.plan_pulls(n, learner_ids, dsts, dst_dtype, ts_after, write))
         return rc;
     if (int rc = check_dsts(ps, n, dsts, dst_dtype)) return rc;
+    ps->proto.prepare_pulls(n, learner_ids);
     if (int rc = use_device(ps)) return rc;
     if (!write.empty())
         if (int rc = order_after_pulls(ps)) return rc;

@@ -13,15 +13,30 @@
 //                          blocks per CU, group
 //   host_fail_launch(i)    the launch that would be logged as the i-th (and no other)
 //                          fails, and does nothing; -1: none
+//   host_fail_alloc(i)     the i-th allocation from now on that the server makes throws;
+//                          -1: none. Returns what was left of the count before
 #include <hip/hip_runtime_api.h>
 #include <sys/mman.h>
 
 #include <cstdlib>
 #include <cstring>
 #include <functional>
+#include <new>
 #include <vector>
 
 #include "ps_kernels.h"
+
+static long g_allocs = -1;   // until the one that throws
+static bool g_own = false;   // in this file: none of these throws
+
+void *operator new(size_t n) {
+    if (!g_own && g_allocs >= 0 && g_allocs-- == 0) throw std::bad_alloc();
+    void *p = std::malloc(n ? n : 1);
+    if (!p) throw std::bad_alloc();
+    return p;
+}
+void operator delete(void *p) noexcept { std::free(p); }
+void operator delete(void *p, size_t) noexcept { std::free(p); }
 
 namespace {
 
@@ -36,13 +51,18 @@ bool g_run = true;
 using Work = std::vector<std::function<void()>>;
 Work *g_capture = nullptr;
 
-hipError_t launch(const Logged &l, std::function<void()> work) {
+template <class F>
+hipError_t launch(const Logged &l, F work) {
+    struct Own {
+        Own() { g_own = true; }
+        ~Own() { g_own = false; }
+    } own;
     if (g_fail == static_cast<long>(g_log.size())) {
         g_fail = -1;
         return hipErrorLaunchFailure;
     }
     g_log.push_back(l);
-    if (g_capture) g_capture->push_back(std::move(work));
+    if (g_capture) g_capture->push_back(work);
     else if (g_run) work();
     return hipSuccess;
 }
@@ -179,6 +199,11 @@ void host_reset(int run) {
 int host_launches(void) { return static_cast<int>(g_log.size()); }
 void host_launch(int i, int *out) { std::memcpy(out, g_log[i].v, sizeof g_log[i].v); }
 void host_fail_launch(int i) { g_fail = i; }
+long host_fail_alloc(long i) {
+    const long left = g_allocs;
+    g_allocs = i;
+    return left;
+}
 
 // ---------------------------------------------------------------- HIP
 

@@ -169,3 +169,35 @@ def test_after_a_failed_launch_only_the_calls_before_it_are_made(lib, mode, skip
         assert ps.ps_run(a.h, hs.script(ops[done:], mem.base)) == (ps.PS_OK, len(ops) - done)
         assert all_of(a, mem) == end, (fail, done)
         a.close()
+
+
+@pytest.mark.parametrize("mode", [ps.PS_QUEUE_FIFO, ps.PS_QUEUE_ROUND_ROBIN])
+def test_without_memory_no_gradient_is_lost_or_applied_twice(lib, mode):
+    """Whichever allocation of a script throws: PS_ENOMEM, the gradients of the
+    `done` calls are applied once each, and the rest of the script ends as it
+    would have."""
+    fail = 0
+    while True:
+        mem, ref = Memory(9, 14), Memory(9, 14)
+        ops = fail_script(mem)
+        a, b = (hs.Host(lib, 9, momentum=0.9, depth=8, skip=False) for _ in range(2))
+        if mode:
+            for s in (a, b):
+                assert ps.ps_set_queue_mode(s.h, mode, 8) == 0
+        s = hs.script(ops, mem.base)
+        lib.host_fail_alloc(fail)
+        rc, done = ps.ps_run(a.h, s)
+        if lib.host_fail_alloc(-1) >= 0:   # there are no more
+            assert rc == ps.PS_OK and fail > 50
+            break
+        assert (rc == ps.PS_ENOMEM and done < len(ops)) or (rc, done) == (ps.PS_OK, len(ops))
+        assert one_by_one(b, ops[:done], ref.base) == (ps.PS_OK, done)
+        assert a.w().tobytes() == b.w().tobytes() and a.v().tobytes() == b.v().tobytes(), fail
+        assert ps.ps_timestamp(a.h) == ps.ps_timestamp(b.h), fail
+        assert ps.ps_pending(a.h) == ps.ps_pending(b.h), fail
+        assert ps.ps_run(a.h, hs.script(ops[done:], mem.base)) == (ps.PS_OK, len(ops) - done)
+        assert one_by_one(b, ops[done:], ref.base) == (ps.PS_OK, len(ops) - done)
+        assert a.w().tobytes() == b.w().tobytes() and mem.a.tobytes() == ref.a.tobytes(), fail
+        a.close()
+        b.close()
+        fail += 1
