@@ -428,7 +428,9 @@ int ps_run(ps_server *ps, const ps_op *ops, int count, int *done);
  * gradients per apply, replicas written, launch shapes); if not -- say a
  * pull that was written at capture would now be skipped -- it returns
  * PS_ESTATE and changes nothing. A call of the script that fails returns
- * its status and changes nothing either.
+ * its status and changes nothing either. If one of several kernels enqueued one
+ * by one fails to launch (PS_EHIP), the calls before it count as made, as ps_run
+ * leaves them; if it is the first, or the graph's launch, nothing has changed.
  *
  * Both need a server stream other than the legacy null stream
  * (ps_set_stream), ordered pulls (no ps_set_pull_stream) and an empty queue

@@ -100,6 +100,11 @@ struct ps_server {
     // progress are recorded here; with plan_only they are not made
     std::vector<LaunchRecord> *record = nullptr;
     bool plan_only = false;
+    // with plan_only: the launch that fails (its place in *record) and how;
+    // kNone: none
+    static constexpr size_t kNone = ~size_t(0);
+    size_t plan_fails = kNone;
+    hipError_t plan_error = hipSuccess;
     StepGroup group;
     // Every call on the handle holds this lock, so several host threads (a
     // push thread per learner, as in Sec. 4.1) may share one server; device
@@ -212,7 +217,12 @@ gadei::Shape shape_for(const ps_server *ps, const gadei::ApplyShape &t) {
     return shape;
 }
 
-// The three kernel launches of the calls, through the recorder.
+// What a launch that was only planned (and recorded) returns.
+hipError_t planned(const ps_server *ps) {
+    return ps->record->size() - 1 == ps->plan_fails ? ps->plan_error : hipSuccess;
+}
+
+// The kernel launches of the calls, through the recorder.
 hipError_t run_apply(ps_server *ps, const gadei::ApplyArgs &a, int gdt, int pdt, int level,
                      const gadei::Shape &shape, bool sync) {
     if (ps->record) {
@@ -227,7 +237,7 @@ hipError_t run_apply(ps_server *ps, const gadei::ApplyArgs &a, int gdt, int pdt,
         static_cast<gadei::ApplyArgs &>(r.apply) = a;
         ps->record->push_back(r);
     }
-    if (ps->plan_only) return hipSuccess;
+    if (ps->plan_only) return planned(ps);
     return sync ? gadei::launch_sync(a, gdt, level, shape, ps->geo, ps->stream)
                 : gadei::launch_apply(a, gdt, pdt, level, shape, ps->geo, ps->stream);
 }
@@ -244,7 +254,7 @@ hipError_t run_steps(ps_server *ps, const gadei::StepsArgs &a, bool sync, int gd
         r.apply = a;
         ps->record->push_back(r);
     }
-    if (ps->plan_only) return hipSuccess;
+    if (ps->plan_only) return planned(ps);
     return gadei::launch_steps(a, sync, gdt, pdt, blocks_per_cu, ps->geo, ps->stream);
 }
 
@@ -258,7 +268,7 @@ hipError_t run_pull(ps_server *ps, const gadei::PullArgs &a, int dtype, int leve
         r.pull = a;
         ps->record->push_back(r);
     }
-    if (ps->plan_only) return hipSuccess;
+    if (ps->plan_only) return planned(ps);
     return gadei::launch_pull(a, dtype, level, ps->geo, s);
 }
 
@@ -658,11 +668,12 @@ namespace {
 // 16.3 vs 6.5, 4 kernels 15.7 vs 11.9, 6 kernels 16.9 vs 18.3).
 constexpr size_t kDirectLaunches = 4;
 
-// Launch a captured plan's kernels as they were captured.
-hipError_t launch_plan(ps_server *ps, const std::vector<LaunchRecord> &plan) {
+// Launch a captured plan's kernels as they were captured; `launched` counts
+// those before the one that failed.
+hipError_t launch_plan(ps_server *ps, const std::vector<LaunchRecord> &plan, size_t &launched) {
     hipError_t e = hipSuccess;
-    for (size_t i = 0; i < plan.size() && e == hipSuccess; ++i) {
-        const LaunchRecord &r = plan[i];
+    for (launched = 0; launched < plan.size(); ++launched) {
+        const LaunchRecord &r = plan[launched];
         gadei::Shape shape;
         shape.blocks_per_cu = r.blocks_per_cu;
         shape.group = r.group;
@@ -679,6 +690,7 @@ hipError_t launch_plan(ps_server *ps, const std::vector<LaunchRecord> &plan) {
                 e = gadei::launch_steps(r.apply, r.kind == 4, r.grad_dtype, r.pull_dtype,
                                         r.blocks_per_cu, ps->geo, ps->stream);
         }
+        if (e != hipSuccess) break;
     }
     return e;
 }
@@ -1419,14 +1431,27 @@ int ps_graph_launch(ps_server *ps, ps_graph *g) {
         const bool direct = g->plan.size() <= kDirectLaunches &&
                             hipStreamIsCapturing(ps->stream, &capturing) == hipSuccess &&
                             capturing == hipStreamCaptureStatusNone;
+        size_t launched = 0;
         const hipError_t e =
-            direct ? launch_plan(ps, g->plan) : hipGraphLaunch(g->exec, ps->stream);
-        if (e != hipSuccess)
-            rc = fail_hip(e, "graph launch");
-        else   // the work is enqueued and committed; the event only serves destroy
+            direct ? launch_plan(ps, g->plan, launched) : hipGraphLaunch(g->exec, ps->stream);
+        if (e == hipSuccess || launched > 0)   // the event only serves destroy
             (void)hipEventRecord(g->done, ps->stream);
+        if (e != hipSuccess) {
+            ps->proto = saved;
+            rc = fail_hip(e, "graph launch");
+            if (launched > 0) {
+                // kernels that went out before the failing one count: the calls
+                // once more, planned as if that launch had failed in ps_run
+                now.clear();
+                ps->plan_fails = launched;
+                ps->plan_error = e;
+                rc = run_recorded(ps, *g, now, true);
+                ps->plan_fails = ps_server::kNone;
+            }
+        }
+    } else {
+        ps->proto = saved;
     }
-    if (rc != PS_OK) ps->proto = saved;
     return rc;
 }
 

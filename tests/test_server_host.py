@@ -201,3 +201,32 @@ def test_without_memory_no_gradient_is_lost_or_applied_twice(lib, mode):
         a.close()
         b.close()
         fail += 1
+
+
+@pytest.mark.parametrize("fail", range(4))
+def test_a_replay_that_fails_half_way_counts_what_it_enqueued(lib, fail):
+    """A replay of four kernels launched one by one, of which the fail-th fails:
+    the server says and holds what the calls before that kernel leave, as ps_run
+    of the script does when that launch fails (before the first one: nothing)."""
+    got = []
+    for graph in (False, True):
+        mem = Memory(9, 14)
+        ops = (pushes(mem, 2) + [("apply",), ("pull", [mem[8]], F32)] + pushes(mem, 2, BF16, at=4) +
+               [("apply_pull", [mem[9], mem[10]], F32), ("pull", [mem[11]], BF16)] +
+               pushes(mem, 1) + [("sync",)])
+        srv = hs.Host(lib, 9, momentum=0.9)
+        s = hs.script(ops, mem.base)
+        if graph:
+            rc, g = ps.ps_graph_create(srv.h, s)
+            assert rc == 0 and len(srv.launches()) == 4
+        srv.clear(fail)
+        before = srv.state()
+        assert (ps.ps_graph_launch(srv.h, g) if graph else ps.ps_run(srv.h, s)[0]) == ps.PS_EHIP
+        assert len(srv.launches()) == fail
+        got.append((srv.state(), srv.w().tobytes(), srv.v().tobytes(), mem.a.tobytes()))
+        if fail == 0:   # (ps_run has made the pushes)
+            got[-1] = (before if not graph else srv.state(), *got[-1][1:])
+        if graph:
+            ps.ps_graph_destroy(g)
+        srv.close()
+    assert got[0] == got[1]
