@@ -357,14 +357,18 @@ bool is_apply(const ps_op &o) {
 
 // The script's calls from `from` on up to its next apply: `next` is that
 // call's index (-1: none, or one of the other kind), with how many gradients
-// are pushed and replicas pulled before it. `same`: every such push could join
-// a group of that gradient dtype.
+// are pushed and replicas pulled before it (more than PS_MAX_REPLICAS: some
+// number above it; the counts are those of calls not yet checked). `same`:
+// every such push could join a group of that gradient dtype.
 struct Ahead {
     int next = -1;
     int pushes = 0;
     int pulls = 0;
     bool same = true;
 };
+int add_pulls(int pulls, const ps_op &o) {
+    return std::min(pulls + std::min(std::max(0, o.count), PS_MAX_REPLICAS + 1), PS_MAX_REPLICAS + 1);
+}
 Ahead look_ahead(const StepGroup &g, int from, int grad_dtype) {
     Ahead h;
     for (int i = from; i < g.count; ++i) {
@@ -373,7 +377,7 @@ Ahead look_ahead(const StepGroup &g, int from, int grad_dtype) {
             ++h.pushes;
             h.same = h.same && o.dtype == grad_dtype && grad_level(o.grad) == 1;
         } else if (o.kind == PS_OP_PULL) {
-            h.pulls += std::max(0, o.count);
+            h.pulls = add_pulls(h.pulls, o);
         } else {
             if (is_apply(o) && (o.kind == PS_OP_APPLY_SYNC) == g.sync) h.next = i;
             break;
@@ -384,8 +388,8 @@ Ahead look_ahead(const StepGroup &g, int from, int grad_dtype) {
 
 // Replicas that the apply at index i of the script and the pulls after it write.
 int pulls_of(const StepGroup &g, int i) {
-    return (g.ops[i].kind == PS_OP_APPLY_PULL ? std::max(0, g.ops[i].count) : 0) +
-           look_ahead(g, i + 1, g.grad_dtype).pulls;
+    const int after = look_ahead(g, i + 1, g.grad_dtype).pulls;
+    return g.ops[i].kind == PS_OP_APPLY_PULL ? add_pulls(after, g.ops[i]) : after;
 }
 
 // Whether the next step of the script will join the group once `r` replicas

@@ -230,3 +230,27 @@ def test_a_replay_that_fails_half_way_counts_what_it_enqueued(lib, fail):
             ps.ps_graph_destroy(g)
         srv.close()
     assert got[0] == got[1]
+
+
+def kinds(srv):
+    return [l.kind for l in srv.launches()]
+
+
+def test_looking_ahead_stops_at_any_count(lib):
+    """Later pulls of absurd counts (refused when the script gets there) do not
+    wrap round to few replicas: the step before them goes out by itself."""
+    n = 10_000_000
+    mem = Memory(4, 20)   # (nothing runs: only the places count)
+    mem.step = 2 * n + 6
+    ops = pushes(mem, 8) + [("apply",), ("pull", [mem[i] for i in range(8, 16)], F32)] + pushes(mem, 8)
+    srv = hs.Host(lib, n, run=False)
+    s = hs.script(ops, mem.base)
+    for _ in range(2):
+        s.pull([0], [mem.base], F32)
+    s.apply()
+    s.build()
+    for i in (-2, -3):
+        s.array[i].count = 2**31 - 1
+    rc, done = ps.ps_run(srv.h, s)
+    assert (rc, done) == (ps.PS_EINVAL, len(ops)) and kinds(srv) == [hs.APPLY, hs.PULL]
+    srv.close()
