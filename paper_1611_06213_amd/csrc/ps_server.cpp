@@ -66,6 +66,7 @@ struct StepGroup {
     int at = 0;           // the call being made
     int first = 0;        // the call whose gradients opened the group
     int pushed = 0;       // pushes since the last apply call
+    size_t left = 0;      // gradients that the last apply left queued
     bool sync = false;    // synchronous steps
     int grad_dtype = PS_F32;
     int pull_dtype = PS_F32;   // of the replicas, once args.r > 0
@@ -393,10 +394,12 @@ int pulls_of(const StepGroup &g, int i) {
 }
 
 // Whether the next step of the script will join the group once `r` replicas
-// pulled now have: as many gradients and replicas as one launch takes.
+// pulled now have: some gradients to apply, and with them no more gradients and
+// replicas than one launch takes.
 bool next_step_joins(const StepGroup &g, int r) {
     const Ahead h = look_ahead(g, g.at + 1, g.grad_dtype);
-    return h.next >= 0 && h.same && g.args.k + g.pushed + h.pushes <= PS_MAX_QUEUE_DEPTH &&
+    return h.next >= 0 && h.same && g.left + g.pushed + h.pushes > 0 &&
+           g.args.k + g.pushed + h.pushes <= PS_MAX_QUEUE_DEPTH &&
            g.args.r + r + h.pulls + pulls_of(g, h.next) <= PS_MAX_REPLICAS;
 }
 
@@ -500,6 +503,7 @@ int launch_batch(ps_server *ps, const std::vector<PushDesc> &items, int pull_dty
     if (std::any_of(items.begin(), items.end(), [](const PushDesc &d) { return d.ready; }))
         if (int rc = flush_group(ps)) return rc;
     if (int rc = wait_ready(ps, items)) return rc;
+    ps->group.left = ps->proto.pending() - items.size();
     gadei::ApplyArgs a;
     std::memset(&a, 0, sizeof a);
     a.w = ps->w;
@@ -946,6 +950,7 @@ int ps_apply_sync(ps_server *ps) {
     if (int rc = ps->proto.plan_sync(b)) return rc;
     const int gdt = b.items.front().dtype;
     if (int rc = use_device(ps)) return rc;
+    ps->group.left = ps->proto.pending() - b.items.size();
     if (ps->group.open &&
         std::all_of(b.items.begin(), b.items.end(), [](const PushDesc &d) {
             return d.ready == nullptr && grad_level(d.grad) == 1;

@@ -254,3 +254,26 @@ def test_looking_ahead_stops_at_any_count(lib):
     rc, done = ps.ps_run(srv.h, s)
     assert (rc, done) == (ps.PS_EINVAL, len(ops)) and kinds(srv) == [hs.APPLY, hs.PULL]
     srv.close()
+
+
+def test_a_step_joins_no_empty_one(lib):
+    """An apply with nothing queued is no step: the replicas before it are
+    written as by a step alone (the fan-out here), unless gradients are left
+    in the queues for it."""
+    n = 10_000_000
+    mem = Memory(4, 40)
+    mem.step = 2 * n + 6
+    step = [("apply",), ("pull", [mem[i] for i in range(16, 24)], F32)]
+    srv = hs.Host(lib, n, run=False, skip=False)
+    assert ps.ps_run(srv.h, hs.script(pushes(mem, 16) + step * 2, mem.base))[0] == 0
+    assert kinds(srv) == [hs.APPLY, hs.PULL, hs.PULL]
+    srv.clear()
+    lib.host_reset(0)
+    assert ps.ps_run(srv.h, hs.script((pushes(mem, 16) + step) * 2, mem.base))[0] == 0
+    assert kinds(srv) == [hs.STEPS]
+    srv.close()
+    srv = hs.Host(lib, n, run=False, skip=False, depth=16)
+    assert ps.ps_set_queue_mode(srv.h, ps.PS_QUEUE_ROUND_ROBIN, 16) == 0
+    assert ps.ps_run(srv.h, hs.script(pushes(mem, 16) * 2 + step * 2, mem.base))[0] == 0
+    assert kinds(srv) == [hs.STEPS]
+    srv.close()
