@@ -249,17 +249,20 @@ int ps_set_queue_mode(ps_server *ps, int mode, int slots_per_learner);
  * and more when at least 8 buffers take part and more than half of the
  * gradient, w and v buffers share one 4 KiB offset (as separately allocated,
  * 2 MiB-aligned buffers do), one front otherwise (ps_alloc_rows buffers). Results are identical either way; only the
- * order in which the grid visits coordinates changes. */
+ * order in which the grid visits coordinates changes. Holds for the joined
+ * launches of a script (ps_run) as for single ones. */
 int ps_set_fronts(ps_server *ps, int fronts_log2);
 
 /* Override the launch shape of the apply (Eq. "asgd") and synchronous-step
  * (Eq. "ssgd") kernels, which is otherwise chosen per call from the number of
- * gradients, momentum, the gradient type and, for shallow applies, the
- * vector's length (tables measured at the VGG-16, Mixed and Text-CNN sizes):
+ * gradients, momentum, the gradient type and the vector's length (tables
+ * measured from 100k to 200M coordinates):
  * blocks_per_cu 1..4 caps the resident 256-thread blocks per compute unit, 0
  * lifts the cap, -1 restores the library's choice; group 4, 8, 12, 16, 24 or
  * 32 sets how many gradients' loads are issued together (the synchronous step
- * takes 16 for 24 and 32), 0 restores the library's choice. Results are
+ * takes 16 for 24 and 32), 0 restores the library's choice. In a script (ps_run,
+ * graphs) the cap holds for joined launches too; with a group set, no calls
+ * join and each takes it. Results are
  * identical for every shape; only speed changes. For callers tuning other
  * sizes. PS_EINVAL for other values, setting unchanged. */
 int ps_set_launch_shape(ps_server *ps, int blocks_per_cu, int group);

@@ -556,13 +556,18 @@ __device__ __forceinline__ void steps_chunk(KernArgs<A> a, uint64_t i) {
     if constexpr (MOM) st_f32<E, nt_wv_st<E>()>(a->v + i, l.v);
 }
 
+// The sweep takes fronts as the apply does (front_block): separately allocated
+// buffers at one offset within 2 MiB, 138M coordinates, 4 steps of 16 gradients
+// and 16 replicas with momentum, us a step: four fronts 2625, one 3131 (a launch
+// per call 3230); 8 and 8: 1070, 1257 (1815).
 template <bool SYNC, bool MOM, int GDT, int PDT, int E, class A>
 __device__ __forceinline__ void steps_sweep() {
     const KernArgs<A> a = (KernArgs<A>)__builtin_amdgcn_kernarg_segment_ptr();
     const uint64_t chunks = a->n / E;
     const uint64_t tid = static_cast<uint64_t>(blockIdx.x) * kBlock + threadIdx.x;
+    const uint64_t vtid = front_block(blockIdx.x, gridDim.x, a->fronts_log2) * kBlock + threadIdx.x;
     const uint64_t stride = static_cast<uint64_t>(gridDim.x) * kBlock;
-    for (uint64_t c = tid; c < chunks; c += stride) steps_chunk<SYNC, MOM, GDT, PDT, E, A>(a, c * E);
+    for (uint64_t c = vtid; c < chunks; c += stride) steps_chunk<SYNC, MOM, GDT, PDT, E, A>(a, c * E);
     if (tid < a->n - chunks * E) steps_chunk<SYNC, MOM, GDT, PDT, 1, A>(a, chunks * E + tid);
 }
 

@@ -336,7 +336,9 @@ int flush_group(ps_server *ps) {
             ps->force_blocks_per_cu >= 0
                 ? ps->force_blocks_per_cu
                 : gadei::steps_blocks_per_cu(a.r * elem_bytes(pdt) / std::max(1, pulls), a.n);
-        e = run_steps(ps, a, sync, gdt, pdt, blocks);
+        gadei::StepsArgs steps = a;
+        steps.fronts_log2 = fronts_for(ps, steps, gdt);
+        e = run_steps(ps, steps, sync, gdt, pdt, blocks);
     }
     if (e == hipSuccess) {
         ps->proto.forget();
@@ -1325,9 +1327,11 @@ int ps_run(ps_server *ps, const ps_op *ops, int count, int *done) {
     if (int rc = check(ps)) return rc;
     if (count < 0 || (count > 0 && ops == nullptr)) return fail(PS_EINVAL, "bad op script");
     PS_LOCK(ps);
-    // Calls may go out together as long as they all run on one stream.
+    // Calls may go out together as long as they all run on one stream, and the
+    // caller has not asked for a gradient group (ps_set_launch_shape), which the
+    // kernels of single steps take.
     StepGroup &g = ps->group;
-    g.open = !ps->pull_lock_free;
+    g.open = !ps->pull_lock_free && ps->force_group == 0;
     g.failed = false;
     g.ops = ops;
     g.count = count;

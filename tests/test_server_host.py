@@ -277,3 +277,33 @@ def test_a_step_joins_no_empty_one(lib):
     assert ps.ps_run(srv.h, hs.script(pushes(mem, 16) * 2 + step * 2, mem.base))[0] == 0
     assert kinds(srv) == [hs.STEPS]
     srv.close()
+
+
+def test_settings_reach_the_steps_of_a_script(lib):
+    """ps_set_fronts and the residency of ps_set_launch_shape hold for a joined
+    launch too; a gradient group asked for leaves every step its own launch,
+    whose loads it arranges."""
+    n = 1_000_000
+    mem = Memory(4, 16)
+    mem.step = 2 * n + 6
+    ops = []
+    for s in range(2):
+        ops += pushes(mem, 4, at=4 * s) + [("apply",), ("pull", [mem[8], mem[9]], F32)]
+    for sync in (False, True):
+        if sync:
+            ops = [("sync",) if o == ("apply",) else o for o in ops]
+        s = hs.script(ops, mem.base)
+        srv = hs.Host(lib, n, momentum=0.9, run=False, skip=False)
+        for f in (0, 3, -1):
+            assert ps.ps_set_fronts(srv.h, f) == 0 and ps.ps_run(srv.h, s)[0] == 0
+        for b in (0, 4, -1):
+            assert ps.ps_set_launch_shape(srv.h, b, 0) == 0 and ps.ps_run(srv.h, s)[0] == 0
+        steps = srv.launches()
+        assert [l.kind for l in steps] == [hs.SYNC_STEPS if sync else hs.STEPS] * 6
+        assert [l.fronts for l in steps] == [0, 3, 0, 0, 0, 0]
+        assert [l.blocks for l in steps] == [steps[0].blocks] * 3 + [0, 4, steps[0].blocks]
+        lib.host_reset(0)
+        assert ps.ps_set_launch_shape(srv.h, -1, 12) == 0 and ps.ps_run(srv.h, s)[0] == 0
+        first = [l for l in srv.launches() if l.kind != hs.PULL]
+        assert [(l.kind, l.k, l.group) for l in first] == [(hs.SYNC if sync else hs.APPLY, 4, 12)] * 2
+        srv.close()
