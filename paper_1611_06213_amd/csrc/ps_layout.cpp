@@ -141,12 +141,19 @@ ApplyShape sync_shape(int k, bool momentum, bool bf16) {
     return {1, 0, 16};
 }
 
-bool steps_join(size_t grad_bytes, size_t pull_bytes, bool momentum, size_t n) {
+bool steps_join(const StepsSize &s, bool momentum, size_t n) {
+    if (s.steps < 2) return false;
+    const size_t steps = static_cast<size_t>(s.steps);
     const size_t saved = (momentum ? 16 : 8) + 4;
-    if (n < 4000000) return true;
-    if (n < kSmallVector)
-        return momentum || grad_bytes <= 8 * saved || pull_bytes >= grad_bytes;
-    return grad_bytes + pull_bytes + saved <= (momentum ? 8 : 6) * saved;
+    if (n >= kSmallVector) {
+        if (s.grad_bytes + s.pull_bytes + steps * saved > (momentum ? 8 : 6) * steps * saved)
+            return false;
+    } else if (n >= 4000000 && !momentum) {
+        if (s.grad_bytes > 8 * steps * saved && s.pull_bytes < s.grad_bytes) return false;
+    }
+    if (s.final_bytes * n <= kCacheBytes) return true;
+    const size_t all = (steps - 1) * saved + (s.pull_bytes - s.final_bytes);
+    return all * (n < kMidVector ? 11 : 7) >= s.grad_bytes + 2 * s.final_bytes;
 }
 
 int steps_blocks_per_cu(size_t bytes, size_t n) {

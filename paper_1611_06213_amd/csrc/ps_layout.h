@@ -106,21 +106,45 @@ ApplyShape apply_shape(int k, bool momentum, bool bf16, size_t n);
 // fronts choice beyond the phase rule: fronts_log2 is 0).
 ApplyShape sync_shape(int k, bool momentum, bool bf16);
 
-// Whether a script's step that reads grad_bytes of gradients and writes
-// pull_bytes of replicas per coordinate is worth joining to its neighbours in
-// one launch (launch_steps). Joining saves a read and a write of w (and v) and
-// the fan-out's read of w per step, and mixes the replicas' writes with the
-// gradients' reads. Always below 4M coordinates, where launches count too;
-// below kSmallVector with momentum, or unless the gradients dwarf both what is
-// saved and the replicas; from there on if it saves an eighth of the step, a
-// sixth without momentum. Measured from server rows, one launch per call
-// against joined, us a step; with momentum: 1M, 1 gradient and 1 pull 5.1 vs
-// 1.2; 17M, 32 and 16: 570 vs 545; 61M, 16 and 10: 1174 vs 934; 138M, 8 and 8:
-// 1786 vs 1333, 16 and 16: 3133 vs 2705, 32 and 16 (a saving of a tenth):
-// 4400-4607 vs 4486-4510. Without: 4M, 4 and 8: 41 vs 28, 32 and 4: 99 vs 99;
-// 17M, 32 and 4: 414 vs 436, 32 and 32: 711 vs 657; 138M, 8 and 8, every step
-// other replicas (a saving of a seventh): 1597 vs 1673.
-bool steps_join(size_t grad_bytes, size_t pull_bytes, bool momentum, size_t n);
+// A launch of several steps of a script (launch_steps), in bytes per
+// coordinate: the gradients it reads, the replicas its steps write, and those of
+// them that stay (a replica that a later step of the launch writes again reaches
+// HBM once).
+struct StepsSize {
+    int steps = 0;
+    size_t grad_bytes = 0;
+    size_t pull_bytes = 0;
+    size_t final_bytes = 0;
+};
+
+// Whether a script's steps are worth joining into this launch. Joining saves a
+// read and a write of w (and v) and the fan-out's read of w per step and the
+// replicas written again, and mixes the writes of those that stay with the
+// gradients' reads. So it must
+//   - save an eighth of an average step from kSmallVector coordinates on, a sixth
+//     without momentum; between 4M and there, without momentum, the gradients must
+//     not dwarf both what is saved and the replicas;
+//   - and save, in all, a seventh of what the launch reads and twice what it
+//     writes for good (an eleventh below kMidVector), unless those writes fit
+//     the memory-side cache (kCacheBytes).
+// Measured from server rows, a launch per call against joined, us a step. The
+// first condition, each step the same replicas, with momentum: 1M, 1 gradient and
+// 1 pull 5.1 vs 1.2; 17M, 32 and 16: 570 vs 545; 61M, 16 and 10: 1162 vs 891;
+// 138M, 8 and 8: 1785 vs 1126, 16 and 16: 3125 vs 2361, 32 and 16 (a saving of a
+// tenth): 4400-4607 vs 4486-4510; bf16 200M, 32 and 32: 4606 vs 4059 (averaged
+// steps 4610 vs 3986), separately allocated 4949 vs 4249. Without: 4M, 4 and 8: 41
+// vs 28, 32 and 4: 99 vs 99; 17M, 32 and 4: 414 vs 436, 32 and 32: 721 vs 663.
+// The second, every step other replicas, with momentum: 138M, 8 and 8 (saved over
+// read and written .16): 1779 vs 1742, 16 and 16 (.08): 3103 vs 3437; 10M, 16 and
+// 16: 237 vs 246-257, 32 and 32 (.03): 435 vs 481; bf16 200M, 32 and 32 (.05): 4659
+// vs 5360, averaged 4633 vs 4942; bf16 138M, 16 and 16 (.16): 1838 vs 1764, 32 and 8
+// (.10): 2261 vs 2305. Half of them again (.37): 61M, 16 and 16: 1362 vs 1201; a
+// quarter again (.13): 10M, 32 and 32: 438 vs 454. Without momentum: 10M, 8 steps of
+// 8 and 8 (.11): 121 vs 130; bf16 17M, 16 and 16 (.09): 224 vs 253; below kMidVector
+// 3.9M, 8 and 8 (.09): 52 vs 46, 16 and 16 (.05): 88 vs 96; 2M, 16 and 16 with
+// momentum (.08; 512 MB): 47 vs 51; 1M (256 MB): 24.6 vs 21.6.
+bool steps_join(const StepsSize &s, bool momentum, size_t n);
+constexpr size_t kCacheBytes = size_t(256) << 20;
 
 // Resident blocks per compute unit of a launch of several steps (launch_steps)
 // whose steps write `bytes` replica bytes per coordinate each: two while they

@@ -67,6 +67,8 @@ struct StepGroup {
     int first = 0;        // the call whose gradients opened the group
     int pushed = 0;       // pushes since the last apply call
     size_t left = 0;      // gradients that the last apply left queued
+    int steps = 0;        // applies whose gradients the group holds
+    int covered = 0;      // the call up to which joining has been found worth it
     bool sync = false;    // synchronous steps
     int grad_dtype = PS_F32;
     int pull_dtype = PS_F32;   // of the replicas, once args.r > 0
@@ -302,6 +304,8 @@ void clear_group(StepGroup &g) {
     std::memset(&g.args, 0, sizeof g.args);
     g.sync = false;
     g.grad_dtype = g.pull_dtype = PS_F32;
+    g.steps = 0;
+    g.covered = -1;
 }
 
 // Enqueue the joined calls. Asynchronous ones with replicas only after the
@@ -358,58 +362,112 @@ bool is_apply(const ps_op &o) {
     return o.kind == PS_OP_APPLY || o.kind == PS_OP_APPLY_PULL || o.kind == PS_OP_APPLY_SYNC;
 }
 
-// The script's calls from `from` on up to its next apply: `next` is that
-// call's index (-1: none, or one of the other kind), with how many gradients
-// are pushed and replicas pulled before it (more than PS_MAX_REPLICAS: some
-// number above it; the counts are those of calls not yet checked). `same`:
-// every such push could join a group of that gradient dtype.
-struct Ahead {
-    int next = -1;
-    int pushes = 0;
-    int pulls = 0;
-    bool same = true;
+// What the group holds and would hold if the calls ahead join it.
+struct Prospect {
+    int steps = 0, k = 0, r = 0;
+    int last = 0;    // the call that its last step ends with
+    int stay = 0;    // replicas that no later step writes again
+    const void *dst[PS_MAX_REPLICAS];   // those
+
+    // Add one call's replicas: false if they do not fit.
+    bool pull(void *const *d, int count) {
+        if (count < 0 || r + static_cast<int64_t>(count) > PS_MAX_REPLICAS || (count > 0 && d == nullptr))
+            return false;
+        for (int i = 0; i < count; ++i)
+            if (std::find(dst, dst + stay, d[i]) == dst + stay) dst[stay++] = d[i];
+        r += count;
+        return true;
+    }
 };
-int add_pulls(int pulls, const ps_op &o) {
-    return std::min(pulls + std::min(std::max(0, o.count), PS_MAX_REPLICAS + 1), PS_MAX_REPLICAS + 1);
+
+Prospect prospect_of(const StepGroup &g) {
+    Prospect p;
+    p.steps = g.steps;
+    p.k = g.args.k;
+    p.last = g.at;
+    p.pull(g.args.dst, g.args.r);
+    return p;
 }
-Ahead look_ahead(const StepGroup &g, int from, int grad_dtype) {
-    Ahead h;
-    for (int i = from; i < g.count; ++i) {
+
+// `now` with the step that the call being made belongs to (g.at: its apply or a
+// pull after it), its further pulls and the steps after it, as far as whole
+// steps fit: gradients of one type for the vector kernels, replicas of
+// pull_dtype. `before` if that step does not fit itself. The calls ahead have not
+// been checked yet.
+Prospect look_ahead(const StepGroup &g, const Prospect &before, Prospect now, int grad_dtype,
+                    int pull_dtype, bool sync) {
+    Prospect whole = before;   // up to a step's end
+    size_t queued = g.left + static_cast<size_t>(g.pushed);
+    for (int i = g.at + 1; i < g.count; ++i) {
         const ps_op &o = g.ops[i];
         if (o.kind == PS_OP_PUSH) {
-            ++h.pushes;
-            h.same = h.same && o.dtype == grad_dtype && grad_level(o.grad) == 1;
-        } else if (o.kind == PS_OP_PULL) {
-            h.pulls = add_pulls(h.pulls, o);
-        } else {
-            if (is_apply(o) && (o.kind == PS_OP_APPLY_SYNC) == g.sync) h.next = i;
-            break;
+            ++queued;
+            // (the next step is none to join; pulls from here on to its apply
+            // are left out)
+            if (o.dtype != grad_dtype || grad_level(o.grad) == 0) break;
+            continue;
         }
+        if (is_apply(o)) {
+            now.last = i - 1;
+            whole = now;
+            if ((o.kind == PS_OP_APPLY_SYNC) != sync) return whole;
+            if (queued > 0) {   // (with nothing queued it is no step)
+                if (now.k + queued > PS_MAX_QUEUE_DEPTH) return whole;
+                now.k += static_cast<int>(queued);
+                ++now.steps;
+                queued = 0;
+            }
+        }
+        if (o.kind == PS_OP_PULL || o.kind == PS_OP_APPLY_PULL) {
+            if (o.count != 0 && (o.dtype != pull_dtype || !now.pull(o.dsts, o.count))) return whole;
+        } else if (!is_apply(o)) {
+            break;   // (an unknown call: the script ends there)
+        }
+        now.last = i;
     }
-    return h;
+    return now;
 }
 
-// Replicas that the apply at index i of the script and the pulls after it write.
-int pulls_of(const StepGroup &g, int i) {
-    const int after = look_ahead(g, i + 1, g.grad_dtype).pulls;
-    return g.ops[i].kind == PS_OP_APPLY_PULL ? add_pulls(after, g.ops[i]) : after;
+// Whether the steps of the prospect are worth one launch (steps_join,
+// ps_layout.h); if so the group need not ask again up to its end.
+bool worth_joining(ps_server *ps, const Prospect &p, int grad_dtype, int pull_dtype) {
+    gadei::StepsSize s;
+    s.steps = p.steps;
+    s.grad_bytes = p.k * elem_bytes(grad_dtype);
+    s.pull_bytes = p.r * elem_bytes(pull_dtype);
+    s.final_bytes = p.stay * elem_bytes(pull_dtype);
+    if (!gadei::steps_join(s, ps->v != nullptr, ps->n)) return false;
+    ps->group.covered = p.last;
+    return true;
 }
 
-// Whether the next step of the script will join the group once `r` replicas
-// pulled now have: some gradients to apply, and with them no more gradients and
-// replicas than one launch takes.
-bool next_step_joins(const StepGroup &g, int r) {
-    const Ahead h = look_ahead(g, g.at + 1, g.grad_dtype);
-    return h.next >= 0 && h.same && g.left + g.pushed + h.pushes > 0 &&
-           g.args.k + g.pushed + h.pushes <= PS_MAX_QUEUE_DEPTH &&
-           g.args.r + r + h.pulls + pulls_of(g, h.next) <= PS_MAX_REPLICAS;
+// Whether the step of the call being made, with `count` gradients, joins the
+// replicas the group holds.
+bool step_joins(ps_server *ps, int count, int gdt, bool sync) {
+    StepGroup &g = ps->group;
+    if (g.at <= g.covered) return true;
+    const Prospect before = prospect_of(g);
+    Prospect now = before;
+    now.k += count;
+    ++now.steps;
+    const ps_op &o = g.ops[g.at];
+    if (o.kind == PS_OP_APPLY_PULL && o.count != 0 &&
+        (o.dtype != g.pull_dtype || !now.pull(o.dsts, o.count)))
+        return false;
+    const Prospect p = look_ahead(g, before, now, gdt, g.pull_dtype, sync);
+    return p.steps > before.steps && worth_joining(ps, p, gdt, g.pull_dtype);
 }
 
-// Whether a step of k gradients and r replicas is worth joining to another
-// (steps_join, ps_layout.h).
-bool joining_saves(const ps_server *ps, int k, int grad_dtype, int r, int pull_dtype) {
-    return gadei::steps_join(k * elem_bytes(grad_dtype), r * elem_bytes(pull_dtype),
-                             ps->v != nullptr, ps->n);
+// Whether replicas pulled now, the group's first, are worth writing from it
+// because steps ahead will join.
+bool pulls_join(ps_server *ps, void *const *dsts, int dtype, const std::vector<int> &write) {
+    StepGroup &g = ps->group;
+    const Prospect before = prospect_of(g);
+    Prospect now = before;
+    for (int i : write)
+        if (!now.pull(&dsts[i], 1)) return false;
+    const Prospect p = look_ahead(g, before, now, g.grad_dtype, dtype, g.sync);
+    return p.steps > before.steps && worth_joining(ps, p, g.grad_dtype, dtype);
 }
 
 // Add the gradients of an apply or synchronous step (one dtype, vector level) to the group,
@@ -424,9 +482,7 @@ int join_gradients(ps_server *ps, const PushDesc *d, int count, int gdt, bool sy
     bool fits = g.args.k == 0 ||
                 (g.sync == sync && g.grad_dtype == gdt && g.args.k + count <= PS_MAX_QUEUE_DEPTH);
     if (fits && g.args.r > 0) {
-        const int pulls = pulls_of(g, g.at);
-        fits = g.args.r + pulls <= PS_MAX_REPLICAS &&
-               joining_saves(ps, count, gdt, pulls, g.pull_dtype);
+        fits = step_joins(ps, count, gdt, sync);
         const size_t gb = ps->n * elem_bytes(gdt), rb = ps->n * elem_bytes(g.pull_dtype);
         for (int i = 0; fits && i < count; ++i)
             for (int r = 0; fits && r < g.args.r; ++r)
@@ -451,6 +507,7 @@ int join_gradients(ps_server *ps, const PushDesc *d, int count, int gdt, bool sy
                        g.args.r | (sync && i == count - 1 ? gadei::kLastOfStep : 0));
         ++g.args.k;
     }
+    ++g.steps;
     return PS_OK;
 }
 
@@ -468,8 +525,7 @@ bool join_pulls(ps_server *ps, void *const *dsts, int dtype, const std::vector<i
                            ? r <= ps->fuse_max_r
                            : g.args.r > 0 ||
                                  (!g.sync && gadei::fuse_replicas(r, g.args.k, ps->n)) ||
-                                 (joining_saves(ps, g.args.k, g.grad_dtype, r, dtype) &&
-                                  next_step_joins(g, r));
+                                 pulls_join(ps, dsts, dtype, write);
     if (!worth) return false;
     const size_t rb = ps->n * elem_bytes(dtype), gb = ps->n * elem_bytes(g.grad_dtype);
     for (size_t i = 0; i < write.size(); ++i) {

@@ -18,6 +18,9 @@
 //   sync_shape K M B      the same for a synchronous step over K learners
 //   fuse R K [N]          1 if ps_apply_pull writes R replicas from the apply of K gradients
 //                         over N coordinates (default 138,357,544)
+//   join S G P F M [N]    1 if S steps of G gradient bytes and P replica bytes a coordinate,
+//                         F of which stay, join in one launch (M = 1: momentum) over N
+//                         coordinates (default 138,357,544)
 #include <cstdio>
 #include <iostream>
 #include <sstream>
@@ -166,6 +169,13 @@ int main() {
             if (!(in >> n)) n = 138357544;
             std::printf("fuse %d",
                         gadei::fuse_replicas(static_cast<int>(r), static_cast<int>(k), n) ? 1 : 0);
+        } else if (cmd == "join") {
+            gadei::StepsSize s;
+            long m;
+            size_t n = 138357544;
+            in >> s.steps >> s.grad_bytes >> s.pull_bytes >> s.final_bytes >> m;
+            if (!(in >> n)) n = 138357544;
+            std::printf("join %d", gadei::steps_join(s, m != 0, n) ? 1 : 0);
         } else if (cmd == "shape" || cmd == "sync_shape") {
             long k, m, b = 0;
             size_t n = 138357544;

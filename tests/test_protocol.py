@@ -304,6 +304,30 @@ def test_small_vector_rules(driver):
     assert got == [f"fuse {v}" for v in fuse.values()]
 
 
+def test_joining_rule(driver):
+    """Which steps of a script go out in one launch: (steps, gradients and
+    replicas a step, replicas that stay of all, bytes of a value, momentum,
+    coordinates). One step never joins; replicas written again help, those that
+    stay cost."""
+    vgg, mixed = 138_357_544, 200_000_000
+    want = {(1, 16, 16, 16, 4, 1, vgg): 0,
+            # the same replicas each step
+            (4, 16, 16, 16, 4, 1, vgg): 1, (2, 32, 16, 16, 4, 1, vgg): 0, (2, 32, 32, 32, 2, 1, mixed): 1,
+            (4, 8, 8, 8, 4, 0, vgg): 0, (4, 8, 8, 8, 4, 0, 17_294_693): 1, (2, 32, 4, 4, 4, 0, 17_294_693): 0,
+            (2, 32, 4, 4, 4, 0, 3_999_999): 1, (2, 32, 4, 4, 4, 0, 4_000_000): 0,
+            (4, 16, 10, 10, 4, 1, 61_100_840): 1,
+            # other replicas each step
+            (4, 8, 8, 32, 4, 1, vgg): 1, (4, 16, 16, 64, 4, 1, vgg): 0, (2, 32, 32, 64, 2, 1, mixed): 0,
+            (4, 16, 16, 64, 2, 1, vgg): 1, (8, 8, 8, 64, 4, 0, 10_000_000): 0, (8, 8, 8, 64, 4, 0, 3_900_000): 1,
+            (4, 16, 16, 64, 4, 1, 2_000_000): 0, (4, 16, 16, 64, 4, 1, 1 << 20): 1,
+            (4, 16, 16, 64, 4, 1, (1 << 20) + 1): 0,
+            # some of them again
+            (4, 16, 16, 32, 4, 1, vgg): 1, (2, 32, 32, 48, 4, 1, 10_000_000): 0}
+    got = run_driver(driver, [f"join {s} {s * k * b} {s * r * b} {f * b} {m} {n}"
+                              for (s, k, r, f, b, m, n) in want])
+    assert got == [f"join {v}" for v in want.values()]
+
+
 def test_replica_fusion_rule(driver):
     """ps_apply_pull writes one replica from the apply pass always, up to 4
     when the apply folds at most 16 gradients, up to 6 when it folds at most 8

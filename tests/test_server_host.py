@@ -307,3 +307,40 @@ def test_settings_reach_the_steps_of_a_script(lib):
         first = [l for l in srv.launches() if l.kind != hs.PULL]
         assert [(l.kind, l.k, l.group) for l in first] == [(hs.SYNC if sync else hs.APPLY, 4, 12)] * 2
         srv.close()
+
+
+@pytest.mark.parametrize("n,k,r,dt", [(HEADLINE, 16, 16, F32), (LARGE, 32, 32, BF16), (10_000_000, 16, 16, F32)])
+@pytest.mark.parametrize("rule", ["apply", "sync", "fused"])
+def test_steps_with_many_replicas_join_if_they_are_written_again(lib, n, k, r, dt, rule):
+    """Steps that write the same replicas share launches; steps that write 16
+    fp32 or 32 bf16 others each go out by themselves (measured slower joined),
+    whatever call the replicas are pulled by."""
+    steps = 128 // k
+    mem = Memory(4, 64 + 64)
+    mem.step = 2 * n + 6
+    for other in (False, True):
+        ops = []
+        for s in range(steps):
+            dsts = [mem[64 + (s * r * other + j) % 64] for j in range(r)]
+            ops += pushes(mem, k, dt) + ([("apply_pull", dsts, dt)] if rule == "fused" else
+                                         [(rule,), ("pull", dsts, dt)])
+        srv = hs.Host(lib, n, momentum=0.9, run=False, skip=False)
+        assert ps.ps_run(srv.h, hs.script(ops, mem.base))[0] == 0
+        one = [hs.SYNC if rule == "sync" else hs.APPLY, hs.PULL]
+        joined = hs.SYNC_STEPS if rule == "sync" else hs.STEPS
+        assert kinds(srv) == (one * steps if other else [joined] * (steps * k // 64))
+        srv.close()
+
+
+def test_replicas_in_rotation_join(lib):
+    """Two sets of replicas in turn: half of what the launch writes is written
+    again in it."""
+    mem = Memory(4, 100)
+    mem.step = 2 * HEADLINE + 6
+    ops = []
+    for s in range(4):
+        ops += pushes(mem, 16) + [("apply",), ("pull", [mem[64 + 16 * (s % 2) + j] for j in range(16)], F32)]
+    srv = hs.Host(lib, HEADLINE, momentum=0.9, run=False, skip=False)
+    assert ps.ps_run(srv.h, hs.script(ops, mem.base))[0] == 0
+    assert [(l.kind, l.k, l.r) for l in srv.launches()] == [(hs.STEPS, 64, 64)]
+    srv.close()
