@@ -156,7 +156,10 @@ bool steps_join(const StepsSize &s, bool momentum, size_t n) {
     return all * (n < kMidVector ? 11 : 7) >= s.grad_bytes + 2 * s.final_bytes;
 }
 
-int steps_blocks_per_cu(size_t bytes, size_t n) {
+int steps_blocks_per_cu(int replicas, size_t pull_elem, size_t grad_elem, size_t n) {
+    const size_t bytes = static_cast<size_t>(replicas) * pull_elem;
+    const size_t blocks = n * grad_elem / (16 * 256);   // a lane's chunk: 16 bytes of gradient
+    if (blocks <= 512 || (blocks <= 1024 && replicas >= 16)) return 2;
     return bytes <= 8 || (bytes <= 16 && n < 8000000) ? 2 : 1;
 }
 

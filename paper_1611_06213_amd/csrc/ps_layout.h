@@ -147,14 +147,21 @@ bool steps_join(const StepsSize &s, bool momentum, size_t n);
 constexpr size_t kCacheBytes = size_t(256) << 20;
 
 // Resident blocks per compute unit of a launch of several steps (launch_steps)
-// whose steps write `bytes` replica bytes per coordinate each: two while they
-// write little, one beyond (more waves then keep more half-written lines of
-// more replicas in cache than it holds). From server rows with momentum, two
-// against one: 60M coordinates, 2 gradients and 4 bf16 replicas a step 573 vs
-// 696 us (4 steps), 1 and 1 fp32 479 vs 502 us; 2 and 4 fp32 957 vs 936, 8 and
-// 8 fp32 2062 vs 1916; 4M, 2 and 4 fp32 202 vs 207 us (16 steps), 8 and 8 fp32
-// 506 vs 455; 1M, 1 and 16 fp32 79.8 vs 71.0 us (8 steps).
-int steps_blocks_per_cu(size_t bytes, size_t n);
+// whose steps write `replicas` replicas each, pull_elem and grad_elem bytes a
+// value: two while they write little, one beyond (more waves then keep more
+// half-written lines of more replicas in cache than it holds). From server rows
+// with momentum, two against one: 60M coordinates, 2 gradients and 4 bf16 replicas
+// a step 573 vs 696 us (4 steps), 1 and 1 fp32 479 vs 502 us; 2 and 4 fp32 957 vs
+// 936, 8 and 8 fp32 2062 vs 1916; 4M, 2 and 4 fp32 202 vs 207 us (16 steps), 8 and
+// 8 fp32 506 vs 455; 1M, 1 and 16 fp32 79.8 vs 71.0 us (8 steps).
+// Two also for launches so short that one would only make the same blocks wait
+// for a round of their own: up to 512 blocks, and up to 1024 where a step writes 16
+// or more (us a step, two against one, a launch per call): 500k fp32, 32 and 32
+// 21.5 vs 24.4 (22.3), 32 and 8 13.1 vs 14.2 (15.7); 1M bf16, 32 and 32 22.6 vs 26.4
+// (24.6), 8 and 8 4.6 vs 4.6; 1M fp32 (976 blocks), 32 and 32 40.7 vs 44.1 (43.9), 8
+// and 8 8.3 vs 7.8 (15.0); 2M bf16, 32 and 32 42.3 vs 47.5 (48.3). From 1,465 on even:
+// 1.5M fp32, 32 and 32 62.3 vs 62.7.
+int steps_blocks_per_cu(int replicas, size_t pull_elem, size_t grad_elem, size_t n);
 
 // Whether ps_apply_pull writes its r replicas from the apply pass over k
 // gradients of an n-coordinate vector (else the apply is followed by the

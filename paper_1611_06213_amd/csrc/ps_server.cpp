@@ -339,7 +339,8 @@ int flush_group(ps_server *ps) {
         const int blocks =
             ps->force_blocks_per_cu >= 0
                 ? ps->force_blocks_per_cu
-                : gadei::steps_blocks_per_cu(a.r * elem_bytes(pdt) / std::max(1, pulls), a.n);
+                : gadei::steps_blocks_per_cu(a.r / std::max(1, pulls), elem_bytes(pdt),
+                                             elem_bytes(gdt), a.n);
         gadei::StepsArgs steps = a;
         steps.fronts_log2 = fronts_for(ps, steps, gdt);
         e = run_steps(ps, steps, sync, gdt, pdt, blocks);

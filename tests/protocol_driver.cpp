@@ -21,6 +21,8 @@
 //   join S G P F M [N]    1 if S steps of G gradient bytes and P replica bytes a coordinate,
 //                         F of which stay, join in one launch (M = 1: momentum) over N
 //                         coordinates (default 138,357,544)
+//   blocks R P G N        resident blocks per compute unit of joined steps of R replicas of P
+//                         bytes a value, gradients of G, over N coordinates
 #include <cstdio>
 #include <iostream>
 #include <sstream>
@@ -176,6 +178,11 @@ int main() {
             in >> s.steps >> s.grad_bytes >> s.pull_bytes >> s.final_bytes >> m;
             if (!(in >> n)) n = 138357544;
             std::printf("join %d", gadei::steps_join(s, m != 0, n) ? 1 : 0);
+        } else if (cmd == "blocks") {
+            int r;
+            size_t pe, ge, n;
+            in >> r >> pe >> ge >> n;
+            std::printf("blocks %d", gadei::steps_blocks_per_cu(r, pe, ge, n));
         } else if (cmd == "shape" || cmd == "sync_shape") {
             long k, m, b = 0;
             size_t n = 138357544;

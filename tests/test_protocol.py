@@ -328,6 +328,19 @@ def test_joining_rule(driver):
     assert got == [f"join {v}" for v in want.values()]
 
 
+def test_joined_residency_rule(driver):
+    """(replicas a step, their bytes, the gradients', coordinates): two blocks
+    per compute unit where little is written or the launch is short."""
+    M = 1 << 20   # 1024 blocks of 4 fp32 a lane, 512 of 8 bf16
+    want = {(32, 4, 4, M // 2 + 1023): 2, (8, 4, 4, M // 2 + 1023): 2, (8, 4, 4, M // 2 + 1024): 1,
+            (16, 4, 4, M + 1023): 2, (15, 4, 4, M + 1023): 1, (32, 4, 4, M + 1024): 1,
+            (8, 2, 2, M + 2047): 2, (16, 2, 2, 2 * M + 2047): 2, (16, 2, 2, 2 * M + 2048): 1,
+            (2, 4, 4, 60_000_000): 2, (3, 4, 4, 60_000_000): 1, (4, 4, 4, 7_999_999): 2,
+            (4, 4, 4, 8_000_000): 1, (0, 4, 4, 60_000_000): 2}
+    got = run_driver(driver, [f"blocks {r} {p} {g} {n}" for (r, p, g, n) in want])
+    assert got == [f"blocks {v}" for v in want.values()]
+
+
 def test_replica_fusion_rule(driver):
     """ps_apply_pull writes one replica from the apply pass always, up to 4
     when the apply folds at most 16 gradients, up to 6 when it folds at most 8
