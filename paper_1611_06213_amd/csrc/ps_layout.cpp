@@ -163,7 +163,8 @@ int steps_blocks_per_cu(int replicas, size_t pull_elem, size_t grad_elem, size_t
     return bytes <= 8 || (bytes <= 16 && n < 8000000) ? 2 : 1;
 }
 
-bool fuse_replicas(int r, int k, size_t n) {
+bool fuse_replicas(int r, int k, size_t n, bool widened) {
+    if (widened && n >= kMidVector && r > 2 && k > 4) return false;
     if (r <= 1 || (r <= 4 && k <= 16) || (r <= 6 && k <= 8 && n < kSmallVector)) return true;
     if (n < kTinyVector) return true;
     if (n < 1500000) return r <= 4 || r * k <= 128;

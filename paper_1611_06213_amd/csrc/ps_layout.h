@@ -175,7 +175,8 @@ int steps_blocks_per_cu(int replicas, size_t pull_elem, size_t grad_elem, size_t
 // r = 8 54.9 vs 54.3); below 1.5M as long as there are few of one or the
 // other (1M: k = 1, r = 16 14.2 vs 16.0; k = 32, r = 4 28.4 vs 30.0, r = 16 36.9
 // vs 35.1); below kTinyVector always (100k: k = 1, r = 2 5.5 vs 8.1; k = 32, r =
-// 16 30.0 vs 33.5). Writing replicas from
+// 16 30.0 vs 33.5; up to 499k and k = 64, r = 64 at most even but for that one corner, fp32
+// 45.0 vs 42.3). Writing replicas from
 // the apply adds write streams to its read streams, which costs more than a
 // separate fan-out once there are many of either; for few of both it saves
 // the fan-out's launch and its second read of w. Measured from server rows
@@ -183,6 +184,11 @@ int steps_blocks_per_cu(int replicas, size_t pull_elem, size_t grad_elem, size_t
 // 0.079 vs 0.086 ms, 138M 1.07 vs 1.10 ms; k = 16, r = 2: 138M 1.89-1.90 vs
 // 1.93-1.94 ms; k = 16, r = 8: 138M 2.47 vs 2.42-2.43 ms; k = 32, r = 2:
 // 61M 1.55 vs 1.51 ms.
-bool fuse_replicas(int r, int k, size_t n);
+// `widened` (bf16 gradients without momentum, fp32 replicas, whose 8-coordinate
+// lanes write each in two stores 32 bytes apart): from kMidVector on at most 2
+// replicas of more than 4 gradients (k = 8, r = 4: 10M 75 vs 76, 61M 447 vs 431, 138M
+// 1182 vs 955 us; r = 2 785 vs 782; k = 16, r = 4 10M 105 vs 101, 138M 1448 vs 1336;
+// k = 4, r = 4 814 vs 813; with momentum k = 8, r = 4 1143 vs 1160).
+bool fuse_replicas(int r, int k, size_t n, bool widened = false);
 
 }  // namespace gadei

@@ -220,6 +220,12 @@ gadei::Shape shape_for(const ps_server *ps, const gadei::ApplyShape &t) {
     return shape;
 }
 
+// fuse_replicas for r replicas of an apply of k gradients of this server.
+bool fuses(const ps_server *ps, int r, int k, int grad_dtype, int pull_dtype) {
+    return gadei::fuse_replicas(
+        r, k, ps->n, grad_dtype == PS_BF16 && pull_dtype == PS_F32 && ps->v == nullptr);
+}
+
 // What a launch that was only planned (and recorded) returns.
 hipError_t planned(const ps_server *ps) {
     return ps->record->size() - 1 == ps->plan_fails ? ps->plan_error : hipSuccess;
@@ -525,7 +531,7 @@ bool join_pulls(ps_server *ps, void *const *dsts, int dtype, const std::vector<i
     const bool worth = ps->fuse_max_r >= 0
                            ? r <= ps->fuse_max_r
                            : g.args.r > 0 ||
-                                 (!g.sync && gadei::fuse_replicas(r, g.args.k, ps->n)) ||
+                                 (!g.sync && fuses(ps, r, g.args.k, g.grad_dtype, dtype)) ||
                                  pulls_join(ps, dsts, dtype, write);
     if (!worth) return false;
     const size_t rb = ps->n * elem_bytes(dtype), gb = ps->n * elem_bytes(g.grad_dtype);
@@ -1083,7 +1089,8 @@ int ps_apply_pull(ps_server *ps, int n, const int *learner_ids, void *const *dst
         if (int rc = order_after_pulls(ps)) return rc;
     const int r = static_cast<int>(write.size());
     const bool fuse = ps->fuse_max_r >= 0 ? r <= ps->fuse_max_r
-                                           : gadei::fuse_replicas(r, static_cast<int>(b.items.size()), ps->n);
+                                           : fuses(ps, r, static_cast<int>(b.items.size()),
+                                                   b.items.back().dtype, dst_dtype);
     // Gradients for the scalar kernels join no group: in a script too, their
     // replicas are written by the same rule as outside one.
     const bool joins = ps->group.open &&

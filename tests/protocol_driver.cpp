@@ -17,7 +17,8 @@
 //                         over N coordinates (default 138,357,544)
 //   sync_shape K M B      the same for a synchronous step over K learners
 //   fuse R K [N]          1 if ps_apply_pull writes R replicas from the apply of K gradients
-//                         over N coordinates (default 138,357,544)
+//                         over N coordinates (default 138,357,544); a fourth number 1: bf16
+//                         gradients without momentum and fp32 replicas
 //   join S G P F M [N]    1 if S steps of G gradient bytes and P replica bytes a coordinate,
 //                         F of which stay, join in one launch (M = 1: momentum) over N
 //                         coordinates (default 138,357,544)
@@ -169,8 +170,12 @@ int main() {
             size_t n = 138357544;
             in >> r >> k;
             if (!(in >> n)) n = 138357544;
-            std::printf("fuse %d",
-                        gadei::fuse_replicas(static_cast<int>(r), static_cast<int>(k), n) ? 1 : 0);
+            int widened = 0;
+            in >> widened;
+            std::printf("fuse %d", gadei::fuse_replicas(static_cast<int>(r), static_cast<int>(k), n,
+                                                        widened != 0)
+                                       ? 1
+                                       : 0);
         } else if (cmd == "join") {
             gadei::StepsSize s;
             long m;

@@ -304,6 +304,15 @@ def test_small_vector_rules(driver):
     assert got == [f"fuse {v}" for v in fuse.values()]
 
 
+def test_replica_fusion_of_widened_gradients(driver):
+    """bf16 gradients without momentum and fp32 replicas: from 5M coordinates on
+    at most two replicas of more than four gradients."""
+    want = {(3, 8, 4_999_999): 1, (3, 8, 5_000_000): 0, (4, 16, 138_357_544): 0, (3, 5, 30_000_000): 0,
+            (4, 4, 30_000_000): 1, (2, 16, 138_357_544): 1, (1, 64, 138_357_544): 1, (5, 8, 10_000_000): 0}
+    got = run_driver(driver, [f"fuse {r} {k} {n} 1" for (r, k, n) in want])
+    assert got == [f"fuse {v}" for v in want.values()]
+
+
 def test_joining_rule(driver):
     """Which steps of a script go out in one launch: (steps, gradients and
     replicas a step, replicas that stay of all, bytes of a value, momentum,

@@ -344,3 +344,19 @@ def test_replicas_in_rotation_join(lib):
     assert ps.ps_run(srv.h, hs.script(ops, mem.base))[0] == 0
     assert [(l.kind, l.k, l.r) for l in srv.launches()] == [(hs.STEPS, 64, 64)]
     srv.close()
+
+
+@pytest.mark.parametrize("m,pdt,fused", [(0.0, F32, False), (0.9, F32, True), (0.0, BF16, True)])
+def test_a_script_writes_replicas_as_the_calls_do(lib, m, pdt, fused):
+    """Four replicas of a single step of 8 bf16 gradients: from the apply, but
+    not fp32 ones without momentum, as measured; by apply_pull and, in a script,
+    by apply and pull."""
+    mem = Memory(4, 16)
+    mem.step = 2 * HEADLINE + 6
+    dsts = [mem[8 + i] for i in range(4)]
+    srv = hs.Host(lib, HEADLINE, momentum=m, run=False, skip=False)
+    for ops in ([("apply_pull", dsts, pdt)], [("apply",), ("pull", dsts, pdt)]):
+        lib.host_reset(0)
+        assert ps.ps_run(srv.h, hs.script(pushes(mem, 8, BF16) + ops, mem.base))[0] == 0
+        assert kinds(srv) == ([hs.APPLY] if fused else [hs.APPLY, hs.PULL])
+    srv.close()
