@@ -50,21 +50,21 @@ namespace {
 ApplyShape small_apply_shape(int k, bool momentum, bool bf16, size_t n) {
     const bool tiny = n < kTinyVector;
     if (bf16) {
-        if (k <= 11 && !momentum) return {k <= 2 ? 4 : 3, 0, 8};
-        if (k <= 23 || tiny) return {2, 0, 16};
-        return {2, 0, 4};
+        if (k <= 11 && !momentum) return {k <= 2 ? 4 : 3, 8};
+        if (k <= 23 || tiny) return {2, 16};
+        return {2, 4};
     }
     if (momentum) {
-        if (k <= 1) return {4, 0, 16};
-        if (k <= 9) return {0, 0, 16};
-        if (k <= 13) return {2, 0, 12};
-        if (k <= 31) return {2, 0, 16};
-        if (k <= 47 && !tiny) return {2, 0, 4};
-        return {1, 0, 32};
+        if (k <= 1) return {4, 16};
+        if (k <= 9) return {0, 16};
+        if (k <= 13) return {2, 12};
+        if (k <= 31) return {2, 16};
+        if (k <= 47 && !tiny) return {2, 4};
+        return {1, 32};
     }
-    if (k <= 9) return {0, 0, 16};
-    if (k <= 31) return {2, 0, 16};
-    return {1, 0, 32};
+    if (k <= 9) return {0, 16};
+    if (k <= 31) return {2, 16};
+    return {1, 32};
 }
 
 }  // namespace
@@ -78,35 +78,35 @@ ApplyShape apply_shape(int k, bool momentum, bool bf16, size_t n) {
     // be waited for before the first (smaller) group.
     if (bf16) {
         if (momentum) {
-            if (k <= 11) return {2, 0, 16};
-            if (k <= 23) return {1, 0, 16};
-            if (k <= 44) return {1, 0, 24};
-            return {1, 0, 16};
+            if (k <= 11) return {2, 16};
+            if (k <= 23) return {1, 16};
+            if (k <= 44) return {1, 24};
+            return {1, 16};
         }
-        if (k <= 11) return {2, 0, 8};
-        if (k <= 23) return {1, 0, 16};
-        if (k <= 31) return {1, 0, 24};
-        if (k <= 47) return {1, 0, 32};
-        if (k <= 56) return {1, 0, 16};
-        return {1, 0, 8};
+        if (k <= 11) return {2, 8};
+        if (k <= 23) return {1, 16};
+        if (k <= 31) return {1, 24};
+        if (k <= 47) return {1, 32};
+        if (k <= 56) return {1, 16};
+        return {1, 8};
     }
     if (momentum) {
-        if (k <= 1) return {4, 0, 16};
-        if (k == 2) return {3, 0, 4};
-        if (k <= 9) return {2, 0, 4};
-        if (k <= 13) return {1, 0, 12};
-        if (k <= 17) return {1, 0, 16};
-        if (k <= 21) return {1, 0, 12};
-        if (k <= 31) return {1, 0, 16};
-        if (k <= 44) return {1, 0, 32};
-        return {1, 0, 8};
+        if (k <= 1) return {4, 16};
+        if (k == 2) return {3, 4};
+        if (k <= 9) return {2, 4};
+        if (k <= 13) return {1, 12};
+        if (k <= 17) return {1, 16};
+        if (k <= 21) return {1, 12};
+        if (k <= 31) return {1, 16};
+        if (k <= 44) return {1, 32};
+        return {1, 8};
     }
-    if (k <= 2) return {0, 0, 16};
-    if (k <= 6) return {3, 0, 4};
-    if (k <= 13) return n < kSmallVector ? ApplyShape{3, 0, 4} : ApplyShape{2, 0, 4};
-    if (k <= 17) return {1, 0, 16};
-    if (k <= 21) return {2, 0, 4};
-    return {1, 0, 8};
+    if (k <= 2) return {0, 16};
+    if (k <= 6) return {3, 4};
+    if (k <= 13) return n < kSmallVector ? ApplyShape{3, 4} : ApplyShape{2, 4};
+    if (k <= 17) return {1, 16};
+    if (k <= 21) return {2, 4};
+    return {1, 8};
 }
 
 ApplyShape sync_shape(int k, bool momentum, bool bf16) {
@@ -115,30 +115,30 @@ ApplyShape sync_shape(int k, bool momentum, bool bf16) {
     // counts between take the next measured one's shape.
     if (bf16) {
         if (momentum) {
-            if (k <= 4) return {3, 0, 16};
-            if (k <= 8) return {2, 0, 12};
-            if (k <= 12) return {2, 0, 4};
-            if (k <= 16) return {1, 0, 16};
-            if (k <= 20) return {1, 0, 12};
-            if (k <= 24) return {1, 0, 16};
-            return {1, 0, 8};
+            if (k <= 4) return {3, 16};
+            if (k <= 8) return {2, 12};
+            if (k <= 12) return {2, 4};
+            if (k <= 16) return {1, 16};
+            if (k <= 20) return {1, 12};
+            if (k <= 24) return {1, 16};
+            return {1, 8};
         }
-        if (k <= 4) return {3, 0, 4};
-        if (k <= 16) return {2, 0, 4};
-        return {1, 0, 12};
+        if (k <= 4) return {3, 4};
+        if (k <= 16) return {2, 4};
+        return {1, 12};
     }
     if (momentum) {
-        if (k <= 4) return {2, 0, 16};
-        if (k <= 8) return {2, 0, 4};
-        if (k <= 12) return {1, 0, 12};
-        if (k <= 16) return {1, 0, 16};
-        if (k <= 20) return {1, 0, 12};
-        if (k <= 24) return {1, 0, 16};
-        return {1, 0, 8};
+        if (k <= 4) return {2, 16};
+        if (k <= 8) return {2, 4};
+        if (k <= 12) return {1, 12};
+        if (k <= 16) return {1, 16};
+        if (k <= 20) return {1, 12};
+        if (k <= 24) return {1, 16};
+        return {1, 8};
     }
-    if (k <= 4) return {3, 0, 16};
-    if (k <= 12) return {2, 0, 4};
-    return {1, 0, 16};
+    if (k <= 4) return {3, 16};
+    if (k <= 12) return {2, 4};
+    return {1, 16};
 }
 
 bool steps_join(const StepsSize &s, bool momentum, size_t n) {

@@ -69,10 +69,9 @@ int fronts_log2_for(const void *const *ptrs, int count);
 constexpr size_t kFrontsBytes = 500000000;
 
 // Launch shape of an apply of k gradients (fp32, or bf16): how many 256-thread
-// blocks one compute unit may hold (0 = as many as fit), for buffers at
-// distinct phases (where fronts_log2_for gives 0) how many fronts to sweep
-// (log2), and how many gradients each lane loads at once (4, 8, 12, 16, 24 or
-// 32; the synchronous step's table stops at 16).
+// blocks one compute unit may hold (0 = as many as fit), and how many gradients
+// each lane loads at once (4, 8, 12, 16, 24 or 32; the synchronous step's table
+// stops at 16).
 // Fewer resident blocks and smaller groups keep fewer DRAM pages and address
 // translations live across the k + 2 streams; too few loads in flight starve
 // the memory system. Chosen from sweeps at the VGG-16 (fp32) and Mixed (bf16)
@@ -82,7 +81,6 @@ constexpr size_t kFrontsBytes = 500000000;
 // bf16 with momentum, k = 24: groups of 24 at one block 79.9, of 16 77.9.
 struct ApplyShape {
     int blocks_per_cu;
-    int fronts_log2;
     int group;
 };
 // n is the vector's length: below kSmallVector coordinates a shallow fp32
@@ -102,8 +100,7 @@ constexpr size_t kMidVector = 5000000;
 constexpr size_t kTinyVector = 500000;
 ApplyShape apply_shape(int k, bool momentum, bool bf16, size_t n);
 
-// The same for a synchronous step over k gradients (one per learner; no
-// fronts choice beyond the phase rule: fronts_log2 is 0).
+// The same for a synchronous step over k gradients (one per learner).
 ApplyShape sync_shape(int k, bool momentum, bool bf16);
 
 // A launch of several steps of a script (launch_steps), in bytes per

@@ -196,7 +196,8 @@ int main() {
             const gadei::ApplyShape sh =
                 cmd == "shape" ? gadei::apply_shape(static_cast<int>(k), m != 0, b != 0, n)
                                : gadei::sync_shape(static_cast<int>(k), m != 0, b != 0);
-            std::printf("%s %d %d %d", cmd.c_str(), sh.blocks_per_cu, sh.fronts_log2, sh.group);
+            // (the second: fronts, log2; no shape asks for more than one)
+            std::printf("%s %d 0 %d", cmd.c_str(), sh.blocks_per_cu, sh.group);
         } else if (cmd == "state") {
             std::printf("state ts=%llu pending=%zu pulls=%llu skipped=%llu smax=%llu ssum=%llu hist=",
                         static_cast<unsigned long long>(p.ts), p.pending(),
