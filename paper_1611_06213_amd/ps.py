@@ -11,6 +11,7 @@ import ctypes
 import os
 import struct
 import threading
+import warnings
 from collections import deque
 from typing import Optional, Sequence
 
@@ -165,6 +166,19 @@ def load_binding():
         from . import _binding
         _native = _binding
     return _native
+
+
+def _per_step_calls():
+    """(push, pulls) of the native binding; where it is not built (or built for
+    another torch), stand-ins that leave every call to the Python route, which
+    makes the same library calls."""
+    try:
+        native = load_binding()
+        return native.push, native.pulls
+    except (RuntimeError, ImportError) as e:
+        warnings.warn(f"per-step calls go through ctypes, which is slower: {e}", RuntimeWarning,
+                      stacklevel=3)
+        return (lambda *_: None,) * 2
 
 
 def _address(f) -> int:
@@ -477,8 +491,7 @@ class ParameterServer:
         self._packed_streams = b""   # of _streams, for the native calls
         # what push, pull and apply call on every step, looked up once
         self._lib = load_library()
-        native = load_binding()
-        self._native_push, self._native_pulls = native.push, native.pulls
+        self._native_push, self._native_pulls = _per_step_calls()
         self._push_fn = _address(self._lib.ps_push_dtype)
         self._pull_many_fn = _address(self._lib.ps_pull_many)
         self._apply_pull_fn = _address(self._lib.ps_apply_pull)

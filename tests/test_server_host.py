@@ -360,3 +360,32 @@ def test_a_script_writes_replicas_as_the_calls_do(lib, m, pdt, fused):
         assert ps.ps_run(srv.h, hs.script(pushes(mem, 8, BF16) + ops, mem.base))[0] == 0
         assert kinds(srv) == ([hs.APPLY] if fused else [hs.APPLY, hs.PULL])
     srv.close()
+
+
+@pytest.mark.parametrize("error", [RuntimeError("not built"), ImportError("undefined symbol")])
+def test_without_the_native_binding_the_python_route_serves(lib, monkeypatch, error):
+    """ParameterServer needs the library alone; it says that its calls are
+    slower."""
+    torch = pytest.importorskip("torch")
+
+    class Device:   # what the binding asks of a device tensor, over host memory
+        is_cuda = True
+        dtype = torch.float32
+
+        def __init__(self, values):
+            self.a = np.array(values, np.float32)
+            self.numel, self.data_ptr = lambda: self.a.size, lambda: self.a.ctypes.data
+            self.is_contiguous = lambda: True
+
+    def missing():
+        raise error
+    lib.host_reset(1)
+    with monkeypatch.context() as m, pytest.warns(RuntimeWarning, match=str(error)):
+        m.setattr(ps, "load_binding", missing)
+        srv = ps.ParameterServer(3, 0.5, queue_depth=2)
+    g, d, e = Device([1, 2, 3]), Device([0] * 3), Device([0] * 3)
+    assert srv.push(0, g) and srv.push(1, g) and not srv.push(2, g)
+    srv.apply_pull([0], [d])
+    srv.pull_many([1], [e])
+    assert d.a.tolist() == e.a.tolist() == [-1, -2, -3] and srv.timestamp == 2 and not srv._pending
+    srv.close()
