@@ -76,7 +76,8 @@ def script_of(ops, base):
     return s.build()
 
 
-def compare(torch, n, m, ops, size, depth=64, seed=0, fusion=None, graph=False):
+def compare(torch, n, m, ops, size, depth=64, seed=0, fusion=None, graph=False, skip=False,
+            fronts=None):
     """Run ops by ps_run (and, with graph, twice more as a HIP graph) on the
     device and in the replay; memory, w and v must be the same bits."""
     rng = np.random.default_rng(seed)
@@ -90,9 +91,11 @@ def compare(torch, n, m, ops, size, depth=64, seed=0, fusion=None, graph=False):
     dw0 = torch.from_numpy(w0).cuda()
     torch.cuda.synchronize()
     srv = ps.ParameterServer(n, 0.01, m, queue_depth=depth, stream=stream)
-    srv.set_pull_skip(False)
+    srv.set_pull_skip(skip)
     if fusion is not None:
         srv.set_pull_fusion(fusion)
+    if fronts is not None:
+        srv.set_fronts(fronts)
     srv.set_weights(dw0)
     script = script_of(ops, dmem.data_ptr())
     ref = Replay(n, 0.01, m, w0, mem)
@@ -176,6 +179,27 @@ def test_synchronous_steps(torch, n, k, r, learners, steps):
         if i == 1:   # both kinds of step in one script
             mixed = ops + [("apply",) if o[0] == "sync" else o for o in ops] + ops
             compare(torch, n, 0.9, mixed, size, seed=n)
+
+
+@pytest.mark.parametrize("fronts", [None, 0, 2, 3])
+@pytest.mark.parametrize("rule", ["apply", "sync"])
+def test_steps_over_many_blocks(torch, rule, fronts):
+    """More blocks than the chip holds at once, in every order of the sweep, with
+    pulls that are skipped as current."""
+    n = 1_300_003   # 1270 blocks of fp32 lanes, 635 of bf16 ones
+    for gdt, pdt in ((F32, F32), (BF16, BF16)):
+        ops, size = regular(n, 3, 4, 3, 4, gdt, pdt, fused=False, apply=rule)
+        ops += [ops[-1], ops[-1]]   # (the learners hold these weights)
+        compare(torch, n, 0.9, ops, size, skip=True, fronts=fronts, graph=fronts is None)
+
+
+def test_steps_that_go_out_one_by_one(torch):
+    """Each step writes eight other replicas of 24 MB: none joins another; where
+    they write the same ones, all do."""
+    n = 6_000_003
+    for learners in (24, 8):
+        ops, size = regular(n, 3, 8, 8, learners, F32, F32, fused=False)
+        compare(torch, n, 0.0, ops, size, skip=True)
 
 
 @pytest.mark.parametrize("align", [1, 2, 4])
