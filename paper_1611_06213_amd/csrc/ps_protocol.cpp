@@ -53,7 +53,6 @@ int Protocol::push(int learner, int dtype, const void *grad, void *ready) {
     const uint64_t lts =
         static_cast<size_t>(learner) < learner_ts.size() ? learner_ts[learner] : 0;
     const PushDesc d{learner, dtype, grad, lts, ready};
-    if (journal_) journal_->room(1);
     if (mode == PS_QUEUE_FIFO) {
         if (static_cast<int>(fifo_.size()) >= depth) {
             stats.pushes_rejected += 1;
@@ -61,6 +60,7 @@ int Protocol::push(int learner, int dtype, const void *grad, void *ready) {
         }
         fifo_.push_back(d);
     } else {
+        if (journal_) journal_->room(1);
         if (static_cast<size_t>(learner) >= rr_.size()) rr_.resize(static_cast<size_t>(learner) + 1);
         auto &q = rr_[learner];
         if (static_cast<int>(q.size()) >= slots) {
@@ -75,9 +75,9 @@ int Protocol::push(int learner, int dtype, const void *grad, void *ready) {
             throw;
         }
         rr_count_ += 1;
+        if (journal_) journal_->queued.push_back({true, d});
     }
     stats.pushes_accepted += 1;
-    if (journal_) journal_->entries.push_back({Journal::Entry::kPushed, learner, d, 0, {}});
     return PS_OK;
 }
 
@@ -141,13 +141,12 @@ int Protocol::plan_sync(Batch &b) const {
 }
 
 void Protocol::consume(const Batch &b) {
-    if (journal_)
-        for (const PushDesc &d : b.items)
-            journal_->entries.push_back({Journal::Entry::kTaken, d.learner, d, 0, {}});
     if (mode == PS_QUEUE_FIFO) {
         fifo_.erase(fifo_.begin(), fifo_.begin() + static_cast<ptrdiff_t>(b.items.size()));
         return;
     }
+    if (journal_)
+        for (const PushDesc &d : b.items) journal_->queued.push_back({false, d});
     for (const auto &t : b.taken) {
         auto &q = rr_[t.first];
         for (int i = 0; i < t.second; ++i) q.pop_front();
@@ -239,8 +238,7 @@ void Protocol::commit_pulls(int n, const int *ids, void *const *dsts, int dtype,
     for (int i = 0; i < n; ++i) {
         grow(ids[i]);
         if (journal_)
-            journal_->entries.push_back({Journal::Entry::kPulled, ids[i], {}, learner_ts[ids[i]],
-                                         last_pull[ids[i]]});
+            journal_->pulls.push_back({ids[i], learner_ts[ids[i]], last_pull[ids[i]]});
         learner_ts[ids[i]] = ts;
     }
     for (int i : write) {
@@ -252,19 +250,29 @@ void Protocol::commit_pulls(int n, const int *ids, void *const *dsts, int dtype,
     }
 }
 
+namespace {
+template <class T>
+void room_for(std::vector<T> &v, size_t count) {
+    const size_t need = v.size() + count;
+    if (need > v.capacity()) v.reserve(std::max(need, 2 * v.capacity()));
+}
+}  // namespace
+
 void Journal::room(size_t count) {
-    const size_t need = entries.size() + count;
-    if (need > entries.capacity()) entries.reserve(std::max(need, 2 * entries.capacity()));
+    room_for(pulls, count);
+    room_for(queued, count);
 }
 
 void Protocol::mark(Journal &j) {
-    j.entries.clear();
+    j.pulls.clear();
+    j.queued.clear();
     j.ts = ts;
     j.last_served = last_served;
     j.learners = learner_ts.size();
     j.stats = stats;
     j.last_staleness = last_staleness;
     j.last_applied = last_applied;
+    j.fifo = fifo_;
     journal_ = &j;
 }
 
@@ -274,26 +282,23 @@ void Protocol::undo() {
     if (journal_ == nullptr) return;
     Journal &j = *journal_;
     journal_ = nullptr;
-    for (auto e = j.entries.rbegin(); e != j.entries.rend(); ++e) {
-        if (e->kind == Journal::Entry::kPulled) {
-            learner_ts[e->learner] = e->learner_ts;
-            last_pull[e->learner] = e->pull;
-        } else if (mode == PS_QUEUE_FIFO) {
-            if (e->kind == Journal::Entry::kPushed) fifo_.pop_back();
-            else fifo_.insert(fifo_.begin(), e->item);
+    for (auto e = j.pulls.rbegin(); e != j.pulls.rend(); ++e) {
+        learner_ts[e->learner] = e->learner_ts;
+        last_pull[e->learner] = e->pull;
+    }
+    for (auto e = j.queued.rbegin(); e != j.queued.rend(); ++e) {
+        auto &q = rr_[e->item.learner];
+        if (e->pushed) {
+            q.pop_back();
+            rr_count_ -= 1;
+            if (q.empty()) waiting_.erase(e->item.learner);
         } else {
-            auto &q = rr_[e->learner];
-            if (e->kind == Journal::Entry::kPushed) {
-                q.pop_back();
-                rr_count_ -= 1;
-                if (q.empty()) waiting_.erase(e->learner);
-            } else {
-                q.push_front(e->item);
-                rr_count_ += 1;
-                waiting_.insert(e->learner);
-            }
+            q.push_front(e->item);
+            rr_count_ += 1;
+            waiting_.insert(e->item.learner);
         }
     }
+    fifo_ = j.fifo;
     learner_ts.resize(j.learners);
     last_pull.resize(j.learners);
     ts = j.ts;

@@ -62,24 +62,29 @@ struct Batch {
 };
 
 // What Protocol::undo needs to put the state back to Protocol::mark: the
-// scalars as they were, and each push, queue removal and pull since.
+// scalars and the FIFO (at most its 64 slots) as they were, and each pull and, of
+// the learners' queues, each push and removal since.
 struct Journal {
-    struct Entry {
-        enum Kind { kPushed, kTaken, kPulled } kind;
+    struct Pulled {
         int learner;
-        PushDesc item;         // kTaken
-        uint64_t learner_ts;   // kPulled: the learner's before the pull
+        uint64_t learner_ts;   // before the pull
         PullKey pull;
     };
-    std::vector<Entry> entries;
+    struct Queued {
+        bool pushed;   // or removed
+        PushDesc item;
+    };
+    std::vector<Pulled> pulls;
+    std::vector<Queued> queued;
     uint64_t ts = 0;
     int last_served = -1;
     size_t learners = 0;
     ps_stats stats{};
     std::vector<int64_t> last_staleness;
     std::vector<int> last_applied;
+    std::vector<PushDesc> fifo;
 
-    // Make room for `count` more entries.
+    // Make room for `count` more pulls and queue entries.
     void room(size_t count);
 };
 

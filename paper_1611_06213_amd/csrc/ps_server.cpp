@@ -370,14 +370,22 @@ bool is_apply(const ps_op &o) {
 }
 
 // What the group holds and would hold if the calls ahead join it.
-struct Prospect {
+struct Extent {
     int steps = 0, k = 0, r = 0;
     int last = 0;    // the call that its last step ends with
     int stay = 0;    // replicas that no later step writes again
-    const void *dst[PS_MAX_REPLICAS];   // those
+};
+struct Prospect : Extent {
+    const void *dst[PS_MAX_REPLICAS];   // the `stay` ones
 
+    explicit Prospect(const StepGroup &g) {
+        steps = g.steps;
+        k = g.args.k;
+        last = g.at;
+        pull(g.args.dst, g.args.r);
+    }
     // Add one call's replicas: false if they do not fit.
-    bool pull(void *const *d, int count) {
+    bool pull(const void *const *d, int count) {
         if (count < 0 || r + static_cast<int64_t>(count) > PS_MAX_REPLICAS || (count > 0 && d == nullptr))
             return false;
         for (int i = 0; i < count; ++i)
@@ -387,23 +395,14 @@ struct Prospect {
     }
 };
 
-Prospect prospect_of(const StepGroup &g) {
-    Prospect p;
-    p.steps = g.steps;
-    p.k = g.args.k;
-    p.last = g.at;
-    p.pull(g.args.dst, g.args.r);
-    return p;
-}
-
 // `now` with the step that the call being made belongs to (g.at: its apply or a
 // pull after it), its further pulls and the steps after it, as far as whole
 // steps fit: gradients of one type for the vector kernels, replicas of
 // pull_dtype. `before` if that step does not fit itself. The calls ahead have not
 // been checked yet.
-Prospect look_ahead(const StepGroup &g, const Prospect &before, Prospect now, int grad_dtype,
-                    int pull_dtype, bool sync) {
-    Prospect whole = before;   // up to a step's end
+Extent look_ahead(const StepGroup &g, const Extent &before, Prospect &now, int grad_dtype,
+                  int pull_dtype, bool sync) {
+    Extent whole = before;   // up to a step's end
     size_t queued = g.left + static_cast<size_t>(g.pushed);
     for (int i = g.at + 1; i < g.count; ++i) {
         const ps_op &o = g.ops[i];
@@ -437,7 +436,7 @@ Prospect look_ahead(const StepGroup &g, const Prospect &before, Prospect now, in
 
 // Whether the steps of the prospect are worth one launch (steps_join,
 // ps_layout.h); if so the group need not ask again up to its end.
-bool worth_joining(ps_server *ps, const Prospect &p, int grad_dtype, int pull_dtype) {
+bool worth_joining(ps_server *ps, const Extent &p, int grad_dtype, int pull_dtype) {
     gadei::StepsSize s;
     s.steps = p.steps;
     s.grad_bytes = p.k * elem_bytes(grad_dtype);
@@ -453,15 +452,15 @@ bool worth_joining(ps_server *ps, const Prospect &p, int grad_dtype, int pull_dt
 bool step_joins(ps_server *ps, int count, int gdt, bool sync) {
     StepGroup &g = ps->group;
     if (g.at <= g.covered) return true;
-    const Prospect before = prospect_of(g);
-    Prospect now = before;
+    Prospect now(g);
+    const Extent before = now;
     now.k += count;
     ++now.steps;
     const ps_op &o = g.ops[g.at];
     if (o.kind == PS_OP_APPLY_PULL && o.count != 0 &&
         (o.dtype != g.pull_dtype || !now.pull(o.dsts, o.count)))
         return false;
-    const Prospect p = look_ahead(g, before, now, gdt, g.pull_dtype, sync);
+    const Extent p = look_ahead(g, before, now, gdt, g.pull_dtype, sync);
     return p.steps > before.steps && worth_joining(ps, p, gdt, g.pull_dtype);
 }
 
@@ -469,11 +468,11 @@ bool step_joins(ps_server *ps, int count, int gdt, bool sync) {
 // because steps ahead will join.
 bool pulls_join(ps_server *ps, void *const *dsts, int dtype, const std::vector<int> &write) {
     StepGroup &g = ps->group;
-    const Prospect before = prospect_of(g);
-    Prospect now = before;
+    Prospect now(g);
+    const Extent before = now;
     for (int i : write)
         if (!now.pull(&dsts[i], 1)) return false;
-    const Prospect p = look_ahead(g, before, now, g.grad_dtype, dtype, g.sync);
+    const Extent p = look_ahead(g, before, now, g.grad_dtype, dtype, g.sync);
     return p.steps > before.steps && worth_joining(ps, p, g.grad_dtype, dtype);
 }
 
@@ -498,7 +497,8 @@ int join_gradients(ps_server *ps, const PushDesc *d, int count, int gdt, bool sy
     if (!fits)
         if (int rc = flush_group(ps)) return rc;
     if (g.args.k == 0) {
-        ps->proto.mark(g.journal);
+        // (the calls of a graph are put back as a whole, but for a replay half made)
+        if (ps->record == nullptr || ps->plan_fails != ps_server::kNone) ps->proto.mark(g.journal);
         g.first = g.at;
         g.sync = sync;
         g.grad_dtype = gdt;
