@@ -55,11 +55,23 @@ KERNEL_SRC = [os.path.join(CSRC, f) for f in ("ps_kernels.hip", "ps_kernels.h", 
 COUNTERS = os.path.join(ROOT, "profiles", "traffic_*.txt")
 
 
+# printed beside the whole-step rates
+JOINED_NOTE = (
+    "bytes_per_step, gbps and pct_peak count the calls of a step as made one by one (w and v "
+    "read and written by each apply, w read by each fan-out). Where ps_run and graph replays "
+    "send consecutive steps out in one launch (ps.h), w and v move once per launch and a "
+    "replica written again in it reaches HBM once: gbps and pct_peak are then effective "
+    "rates that can exceed the peak, and --mode separate and fused time the same launches. "
+    "kernel_ms and roofline are of single calls")
+
+
 def algorithmic_bytes(cfg, mode: str, r: int):
     """Bytes the method must move per step (one apply of K gradients + R
     replica writes): K gradient reads, w read+write, v read+write (momentum),
     R replica writes, plus one more read of w when the pull is its own
-    kernel. Returns (per step, per dominant-kernel launch)."""
+    kernel. Returns (per step, per dominant-kernel launch). These are the bytes
+    of the calls made one by one: a launch that ps_run joins several steps in
+    moves fewer (JOINED_NOTE)."""
     from paper_1611_06213_amd import accounting as acc
     gb = 2 if cfg.grad_dtype == 1 else 4
     rb = 2 if cfg.pull_dtype == 1 else 4
@@ -347,7 +359,9 @@ def main():
     ap.add_argument("--config", default="vgg16")
     ap.add_argument("--mode", choices=["fused", "separate", "hogwild"], default="separate",
                     help="separate: ps_apply_pending + ps_pull_many (one kernel each, timed "
-                         "apart); fused: ps_apply_pull (the same kernels above one replica); "
+                         "apart); fused: ps_apply_pull (the same kernels above one replica); in "
+                         "the runs that give value, ps_run may send the steps of either out "
+                         "joined; "
                          "hogwild: pulls lock-free on a second stream, overlapping the next "
                          "apply (Sec. 4.1)")
     ap.add_argument("--apply", choices=["asgd", "sync"], default="asgd",
@@ -653,6 +667,7 @@ def main():
         "learner_ps_gbps_paper_accounting": round(
             pushes / elapsed * learner_ps_bytes_per_push(n) / 1e9, 1),
         "bytes_per_step": round(step_bytes / args.steps),
+        "bytes_note": JOINED_NOTE,
         # kernel time summed over both streams (with hogwild the two overlap)
         "pushes_per_s_device": round(pushes / ((k_ms + p_ms) * args.steps * 1e-3), 2),
         "kernel_ms": {"apply": round(k_ms, 4), **({"pull": round(p_ms, 4)} if p_ms else {})},
