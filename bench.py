@@ -60,7 +60,7 @@ JOINED_NOTE = (
     "bytes_per_step, gbps and pct_peak count the calls of a step as made one by one (w and v "
     "read and written by each apply, w read by each fan-out). Where ps_run and graph replays "
     "send consecutive steps out in one launch (ps.h), w and v move once per launch and a "
-    "replica written again in it reaches HBM once: gbps and pct_peak are then effective "
+    "replica written again in it may still be in cache: gbps and pct_peak are then effective "
     "rates that can exceed the peak, and --mode separate and fused time the same launches. "
     "kernel_ms and roofline are of single calls")
 

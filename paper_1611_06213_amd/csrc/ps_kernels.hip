@@ -467,11 +467,13 @@ struct StepsLane {
 // followed by the replicas pulled after it: as apply_group (SYNC: sum_group,
 // with the averaged step after the last gradient of each), with the stores
 // of dst[r] .. between the updates. A replica that a later step of this
-// launch writes again is stored with the ordinary policy, so that its line is
-// still in L2 then and reaches HBM once (16 steps of 4 gradients and the same
-// 4 replicas, 4M coordinates: 243 us, 361 with the non-temporal hint); the
-// last write of each carries the hint (all plain: up to 5% slower where
-// every step writes other replicas).
+// launch writes again is stored with the ordinary policy, so that its line may
+// still be in L2 then (16 steps of 4 gradients and the same 4 replicas, 4M
+// coordinates: 243 us, 361 with the non-temporal hint; of 4 steps of 16 gradients
+// and 16 fp32 replicas, 138M, a third of the writes stay there, of 2 steps of 32
+// bf16 ones, 200M, none does: the memory-side cache takes those); the last write
+// of each carries the hint (all plain: up to 5% slower where every step writes
+// other replicas).
 template <bool SYNC, bool MOM, int GDT, int PDT, int E, int G, class A>
 __device__ __forceinline__ void steps_group(KernArgs<A> a, int k0, uint64_t i, StepsLane<E> &l,
                                             float lr, float m) {

@@ -105,8 +105,8 @@ ApplyShape sync_shape(int k, bool momentum, bool bf16);
 
 // A launch of several steps of a script (launch_steps), in bytes per
 // coordinate: the gradients it reads, the replicas its steps write, and those of
-// them that stay (a replica that a later step of the launch writes again reaches
-// HBM once).
+// them that stay (a replica that a later step of the launch writes again is then
+// often still in cache).
 struct StepsSize {
     int steps = 0;
     size_t grad_bytes = 0;
