@@ -287,7 +287,7 @@ hipError_t run_pull(ps_server *ps, const gadei::PullArgs &a, int dtype, int leve
 // the gradients of one batch, lets learners pull, applies the next, and per
 // coordinate the whole sequence needs w and v only at its ends. One launch
 // (launch_steps) reads w and v once for several steps, writes the replicas of
-// each from the pass, and a replica that the next step writes again is still
+// each from the pass, and a replica that the next step writes again is often still
 // in cache then. Where that saves enough is steps_join's rule (ps_layout.h); a
 // single step's replicas follow fuse_replicas.
 
