@@ -69,8 +69,12 @@ ApplyShape small_apply_shape(int k, bool momentum, bool bf16, size_t n) {
 
 }  // namespace
 
-ApplyShape apply_shape(int k, bool momentum, bool bf16, size_t n) {
-    if (n < kMidVector) return small_apply_shape(k, momentum, bf16, n);
+ApplyShape apply_shape(int k, bool momentum, bool bf16, size_t n, bool widened) {
+    if (n < kMidVector) {
+        ApplyShape s = small_apply_shape(k, momentum, bf16, n);
+        if (widened && (s.blocks_per_cu == 0 || s.blocks_per_cu > 2)) s.blocks_per_cu = 2;
+        return s;
+    }
     // Measured at 138,357,544 fp32 / 200,000,000 bf16 parameters for the
     // depths 1, 2, 3, 4, 6, 8, 12, 16, 20, 24, 32, 36, 40, 44, 48 and 64
     // (bf16: from 8); the depths between take a neighbour's shape. A group of
@@ -163,10 +167,22 @@ int steps_blocks_per_cu(int replicas, size_t pull_elem, size_t grad_elem, size_t
     return bytes <= 8 || (bytes <= 16 && n < 8000000) ? 2 : 1;
 }
 
-bool fuse_replicas(int r, int k, size_t n, bool widened) {
-    if (widened && n >= kMidVector && r > 2 && k > 4) return false;
-    if (r <= 1 || (r <= 4 && k <= 16) || (r <= 6 && k <= 8 && n < kSmallVector)) return true;
-    if (n < kTinyVector) return true;
+namespace {
+bool fuses_at_any_size(int r, int k, size_t n) {
+    return r <= 1 || (r <= 4 && k <= 16) || (r <= 6 && k <= 8 && n < kSmallVector);
+}
+}  // namespace
+
+bool fuse_replicas(int r, int k, bool bf16, bool fp32_replicas, bool momentum, size_t n) {
+    const bool widened = bf16 && fp32_replicas;
+    if (fuses_at_any_size(r, k, n))
+        return !(widened && !momentum && n >= kMidVector && r > 2 && k > 4);
+    if (fp32_replicas && r * n > (widened ? kWidenedFused : kFusedReplicas)) return false;
+    return fuse_replicas(r, k, n);
+}
+
+bool fuse_replicas(int r, int k, size_t n) {
+    if (fuses_at_any_size(r, k, n) || n < kTinyVector) return true;
     if (n < 1500000) return r <= 4 || r * k <= 128;
     return n < 3000000 && r <= 8 && k <= 16;
 }

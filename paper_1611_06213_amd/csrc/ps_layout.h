@@ -94,11 +94,17 @@ constexpr size_t kSmallVector = 20000000;
 // fp32 with momentum k = 4 7.8 -> 6.9 us, 16 16.1 -> 14.9; bf16 with momentum
 // k = 32 17.8 -> 15.0; bf16 k = 64 25.9 -> 22.8; 4M: fp32 with momentum k = 16
 // 54.8 -> 51.7, bf16 with momentum k = 64 98.8 -> 89.8). At 7M the two are
-// within 5% of each other either way. Below kTinyVector one round of blocks holds everything, and all of a
-// lane's loads go out together (100k, fp32 k = 64: 10.2 -> 8.4 us).
+// within 5% of each other either way. Below kTinyVector one round of blocks holds
+// everything, and all of a lane's loads go out together (100k, fp32 k = 64: 10.2
+// -> 8.4 us).
+// `widened`: the launch also writes more than one fp32 replica from bf16
+// gradients. Its 8-coordinate lanes write each in two stores 32 bytes apart, and
+// more than two blocks a unit then keep more half-written lines than L2 holds (no
+// momentum, 1 gradient and 4 replicas: 2M 16.0 us with four, 12.7 with two; 4M 26.1
+// vs 23.4).
 constexpr size_t kMidVector = 5000000;
 constexpr size_t kTinyVector = 500000;
-ApplyShape apply_shape(int k, bool momentum, bool bf16, size_t n);
+ApplyShape apply_shape(int k, bool momentum, bool bf16, size_t n, bool widened = false);
 
 // The same for a synchronous step over k gradients (one per learner).
 ApplyShape sync_shape(int k, bool momentum, bool bf16);
@@ -181,11 +187,19 @@ int steps_blocks_per_cu(int replicas, size_t pull_elem, size_t grad_elem, size_t
 // 0.079 vs 0.086 ms, 138M 1.07 vs 1.10 ms; k = 16, r = 2: 138M 1.89-1.90 vs
 // 1.93-1.94 ms; k = 16, r = 8: 138M 2.47 vs 2.42-2.43 ms; k = 32, r = 2:
 // 61M 1.55 vs 1.51 ms.
-// `widened` (bf16 gradients without momentum, fp32 replicas, whose 8-coordinate
-// lanes write each in two stores 32 bytes apart): from kMidVector on at most 2
-// replicas of more than 4 gradients (k = 8, r = 4: 10M 75 vs 76, 61M 447 vs 431, 138M
-// 1182 vs 955 us; r = 2 785 vs 782; k = 16, r = 4 10M 105 vs 101, 138M 1448 vs 1336;
-// k = 4, r = 4 814 vs 813; with momentum k = 8, r = 4 1143 vs 1160).
-bool fuse_replicas(int r, int k, size_t n, bool widened = false);
+bool fuse_replicas(int r, int k, size_t n);
+// The same by the types too. Beyond what is fused at any size fp32 replicas must
+// fit: 64 MiB of them (1M, k = 1, r = 16: 16.2 us apart, 15.1 fused; 1.4M 21.5,
+// 23.9; k = 10, r = 12 without momentum 24.0, 27.9), and, `widened` (fp32 replicas of
+// bf16 gradients: each lane writes them in two stores 32 bytes apart), what L2
+// merges: 30 MB (700k, k = 1, r = 8: 10.2, 9.5, r = 16 13.4, 17.3; 1M, k = 16, r = 6
+// 15.4, 14.6, k = 4, r = 8 12.6, 16.2; 1.4M, k = 1, r = 16 21.9, 39.2; 2M, k = 1, r = 8
+// 20.3, 30.1). From kMidVector on, widened and without momentum at most 2 replicas
+// of more than 4 gradients (k = 8, r = 4: 10M 75 vs 76, 61M 447 vs 431, 138M 1182 vs
+// 955 us; r = 2 785 vs 782; k = 16, r = 4 10M 105 vs 101, 138M 1448 vs 1336; k = 4, r
+// = 4 814 vs 813; with momentum k = 8, r = 4 1143 vs 1160).
+bool fuse_replicas(int r, int k, bool bf16, bool fp32_replicas, bool momentum, size_t n);
+constexpr size_t kFusedReplicas = size_t(16) << 20;   // coordinates, all replicas
+constexpr size_t kWidenedFused = 7500000;
 
 }  // namespace gadei

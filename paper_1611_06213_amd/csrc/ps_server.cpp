@@ -222,8 +222,16 @@ gadei::Shape shape_for(const ps_server *ps, const gadei::ApplyShape &t) {
 
 // fuse_replicas for r replicas of an apply of k gradients of this server.
 bool fuses(const ps_server *ps, int r, int k, int grad_dtype, int pull_dtype) {
-    return gadei::fuse_replicas(
-        r, k, ps->n, grad_dtype == PS_BF16 && pull_dtype == PS_F32 && ps->v == nullptr);
+    return gadei::fuse_replicas(r, k, grad_dtype == PS_BF16, pull_dtype == PS_F32, ps->v != nullptr,
+                                ps->n);
+}
+
+// The launch shape of an apply of a.k gradients that writes a.r replicas.
+gadei::Shape shape_of(const ps_server *ps, const gadei::ApplyArgs &a, int grad_dtype,
+                      int pull_dtype) {
+    const bool bf16 = grad_dtype == PS_BF16;
+    return shape_for(ps, gadei::apply_shape(a.k, a.v != nullptr, bf16, a.n,
+                                            bf16 && pull_dtype == PS_F32 && a.r > 1));
 }
 
 // What a launch that was only planned (and recorded) returns.
@@ -336,10 +344,9 @@ int flush_group(ps_server *ps) {
     if (plain) {
         gadei::ApplyArgs one = a;
         one.fronts_log2 = fronts_for(ps, one, gdt);
-        const bool bf16 = gdt == PS_BF16;
         const gadei::Shape shape =
-            shape_for(ps, sync ? gadei::sync_shape(one.k, one.v != nullptr, bf16)
-                               : gadei::apply_shape(one.k, one.v != nullptr, bf16, one.n));
+            sync ? shape_for(ps, gadei::sync_shape(one.k, one.v != nullptr, gdt == PS_BF16))
+                 : shape_of(ps, one, gdt, pdt);
         e = run_apply(ps, one, gdt, one.r > 0 ? pdt : -1, 1, shape, sync);
     } else {
         const int blocks =
@@ -597,8 +604,6 @@ int launch_batch(ps_server *ps, const std::vector<PushDesc> &items, int pull_dty
         a.k = static_cast<int>(end - start);
         a.r = 0;
         a.fronts_log2 = fronts_for(ps, a, gdt);
-        const gadei::Shape shape =
-            shape_for(ps, gadei::apply_shape(a.k, a.v != nullptr, gdt == PS_BF16, a.n));
         int pdt = -1;
         if (end == q && pull_dtype >= 0 && !write.empty()) {
             pdt = pull_dtype;
@@ -608,7 +613,7 @@ int launch_batch(ps_server *ps, const std::vector<PushDesc> &items, int pull_dty
                 level = std::min(level, dst_level(a.dst[j], pull_dtype));
             }
         }
-        hipError_t e = run_apply(ps, a, gdt, pdt, level, shape, false);
+        hipError_t e = run_apply(ps, a, gdt, pdt, level, shape_of(ps, a, gdt, pdt), false);
         if (e != hipSuccess) return fail_hip(e, "apply kernel launch");
         start = end;
     }

@@ -17,8 +17,9 @@
 //                         over N coordinates (default 138,357,544)
 //   sync_shape K M B      the same for a synchronous step over K learners
 //   fuse R K [N]          1 if ps_apply_pull writes R replicas from the apply of K gradients
-//                         over N coordinates (default 138,357,544); a fourth number 1: bf16
-//                         gradients without momentum and fp32 replicas
+//                         over N coordinates (default 138,357,544); G [P [M]] after N: by the
+//                         types too, G = 1: bf16 gradients, P = 1: fp32 replicas (default),
+//                         M = 1: momentum
 //   join S G P F M [N]    1 if S steps of G gradient bytes and P replica bytes a coordinate,
 //                         F of which stay, join in one launch (M = 1: momentum) over N
 //                         coordinates (default 138,357,544)
@@ -170,12 +171,16 @@ int main() {
             size_t n = 138357544;
             in >> r >> k;
             if (!(in >> n)) n = 138357544;
-            int widened = 0;
-            in >> widened;
-            std::printf("fuse %d", gadei::fuse_replicas(static_cast<int>(r), static_cast<int>(k), n,
-                                                        widened != 0)
-                                       ? 1
-                                       : 0);
+            int bf16, fp32 = 1, momentum = 0;
+            const int ri = static_cast<int>(r), ki = static_cast<int>(k);
+            const bool typed = static_cast<bool>(in >> bf16);
+            if (!(in >> fp32)) fp32 = 1;
+            in >> momentum;
+            std::printf("fuse %d",
+                        (typed ? gadei::fuse_replicas(ri, ki, bf16 != 0, fp32 != 0, momentum != 0, n)
+                               : gadei::fuse_replicas(ri, ki, n))
+                            ? 1
+                            : 0);
         } else if (cmd == "join") {
             gadei::StepsSize s;
             long m;

@@ -313,6 +313,21 @@ def test_replica_fusion_of_widened_gradients(driver):
     assert got == [f"fuse {v}" for v in want.values()]
 
 
+def test_fused_replicas_must_fit(driver):
+    """(replicas, gradients, coordinates, bf16 gradients, fp32 replicas): of
+    small vectors fp32 replicas join the apply up to 64 MiB in all, 30 MB where
+    the gradients are bf16; what is fused at any size and bf16 replicas, whatever
+    they take."""
+    M = 1 << 20
+    want = {(16, 1, M, 0, 1): 1, (16, 1, M + 1, 0, 1): 0, (16, 1, M + 1, 0, 0): 1, (16, 1, M + 1, 1, 0): 1,
+            (12, 10, 1_400_000, 0, 1): 0, (8, 16, 2_000_000, 0, 1): 1, (8, 8, 2_100_000, 0, 1): 0,
+            (15, 1, 500_000, 1, 1): 1, (15, 1, 500_001, 1, 1): 0, (16, 1, 499_999, 1, 1): 0,
+            (64, 64, 100_000, 1, 1): 1, (8, 8, 1_000_000, 1, 1): 0, (6, 8, 4_000_000, 1, 1): 1,
+            (4, 16, 4_000_000, 1, 1): 1, (8, 16, 2_999_999, 1, 0): 1}
+    got = run_driver(driver, [f"fuse {r} {k} {n} {g} {p}" for (r, k, n, g, p) in want])
+    assert got == [f"fuse {v}" for v in want.values()]
+
+
 def test_joining_rule(driver):
     """Which steps of a script go out in one launch: (steps, gradients and
     replicas a step, replicas that stay of all, bytes of a value, momentum,
