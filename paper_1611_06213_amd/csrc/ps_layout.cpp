@@ -67,6 +67,14 @@ ApplyShape small_apply_shape(int k, bool momentum, bool bf16, size_t n) {
     return {1, 32};
 }
 
+// sync_shape below kMidVector coordinates, fp32 (the same kind of figures; the
+// table of large vectors loses up to 29% there).
+ApplyShape small_sync_shape(int k, bool momentum, size_t n) {
+    if (k <= 4) return {momentum ? 4 : 0, 4};                    // 4%, 5%
+    if (k <= 13) return {4, momentum ? 8 : 4};                   // 6%
+    return {momentum && n >= 3000000 ? 3 : 4, 4};                // 6%
+}
+
 }  // namespace
 
 ApplyShape apply_shape(int k, bool momentum, bool bf16, size_t n, bool widened) {
@@ -113,10 +121,18 @@ ApplyShape apply_shape(int k, bool momentum, bool bf16, size_t n, bool widened) 
     return {1, 8};
 }
 
-ApplyShape sync_shape(int k, bool momentum, bool bf16) {
+ApplyShape sync_shape(int k, bool momentum, bool bf16, size_t n) {
+    if (!bf16 && n >= kTinyVector && n < kMidVector) {
+        if (k <= 27) return small_sync_shape(k, momentum, n);
+        if (n < 3000000) return {2, 4};   // 3% (below: 12%)
+    }
     // Measured at 138,357,544 fp32 / 200,000,000 bf16 parameters with one
     // gradient per learner, for 4, 8, 12, 16, 20, 24 and 32 learners; the
-    // counts between take the next measured one's shape.
+    // counts between take the next measured one's shape. fp32 steps of one and two
+    // learners, and of 17 to 20 without momentum, also from packed odd rows and at 17M
+    // and 61M (17M, two with momentum: 66 us with four blocks, 77 with two; 61M, 20
+    // without: 823-907, 872-952 with one block and groups of 16).
+    if (!bf16 && k <= 2) return momentum || k == 2 ? ApplyShape{4, 16} : ApplyShape{0, 16};
     if (bf16) {
         if (momentum) {
             if (k <= 4) return {3, 16};
@@ -142,6 +158,8 @@ ApplyShape sync_shape(int k, bool momentum, bool bf16) {
     }
     if (k <= 4) return {3, 16};
     if (k <= 12) return {2, 4};
+    if (k <= 16) return {1, 16};
+    if (k <= 20) return {2, 4};
     return {1, 16};
 }
 

@@ -106,8 +106,12 @@ constexpr size_t kMidVector = 5000000;
 constexpr size_t kTinyVector = 500000;
 ApplyShape apply_shape(int k, bool momentum, bool bf16, size_t n, bool widened = false);
 
-// The same for a synchronous step over k gradients (one per learner).
-ApplyShape sync_shape(int k, bool momentum, bool bf16);
+// The same for a synchronous step over k gradients (one per learner). Below
+// kMidVector fp32 steps take shapes of their own, as applies do (packed odd rows,
+// where one coordinate per lane took, without momentum: 1M, k = 16 13.0 us against
+// 14.4 with the table of large vectors and 11.8 now; 2.5M, k = 20 35.4, 42.5, 37.3;
+// with momentum: 4.9M, k = 12 50.5, 58.6, 54.1).
+ApplyShape sync_shape(int k, bool momentum, bool bf16, size_t n);
 
 // A launch of several steps of a script (launch_steps), in bytes per
 // coordinate: the gradients it reads, the replicas its steps write, and those of

@@ -345,7 +345,7 @@ int flush_group(ps_server *ps) {
         gadei::ApplyArgs one = a;
         one.fronts_log2 = fronts_for(ps, one, gdt);
         const gadei::Shape shape =
-            sync ? shape_for(ps, gadei::sync_shape(one.k, one.v != nullptr, gdt == PS_BF16))
+            sync ? shape_for(ps, gadei::sync_shape(one.k, one.v != nullptr, gdt == PS_BF16, one.n))
                  : shape_of(ps, one, gdt, pdt);
         e = run_apply(ps, one, gdt, one.r > 0 ? pdt : -1, 1, shape, sync);
     } else {
@@ -1046,7 +1046,8 @@ int ps_apply_sync(ps_server *ps) {
         level = std::min(level, grad_level(a.g[j]));
     }
     a.fronts_log2 = fronts_for(ps, a, gdt);
-    const gadei::Shape shape = shape_for(ps, gadei::sync_shape(a.k, a.v != nullptr, gdt == PS_BF16));
+    const gadei::Shape shape =
+        shape_for(ps, gadei::sync_shape(a.k, a.v != nullptr, gdt == PS_BF16, a.n));
     hipError_t e = run_apply(ps, a, gdt, -1, level, shape, true);
     if (e != hipSuccess) return fail_hip(e, "synchronous step launch");
     ps->proto.commit_sync(b);

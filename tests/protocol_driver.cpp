@@ -15,7 +15,7 @@
 //   rows B C              row layout of C rows of B bytes: head stride span
 //   shape K M B [N]       launch shape of a K-gradient apply (M = 1: momentum; B = 1: bf16)
 //                         over N coordinates (default 138,357,544)
-//   sync_shape K M B      the same for a synchronous step over K learners
+//   sync_shape K M B [N]  the same for a synchronous step over K learners
 //   fuse R K [N]          1 if ps_apply_pull writes R replicas from the apply of K gradients
 //                         over N coordinates (default 138,357,544); G [P [M]] after N: by the
 //                         types too, G = 1: bf16 gradients, P = 1: fp32 replicas (default),
@@ -200,7 +200,7 @@ int main() {
             if (!(in >> n)) n = 138357544;
             const gadei::ApplyShape sh =
                 cmd == "shape" ? gadei::apply_shape(static_cast<int>(k), m != 0, b != 0, n)
-                               : gadei::sync_shape(static_cast<int>(k), m != 0, b != 0);
+                               : gadei::sync_shape(static_cast<int>(k), m != 0, b != 0, n);
             // (the second: fronts, log2; no shape asks for more than one)
             std::printf("%s %d 0 %d", cmd.c_str(), sh.blocks_per_cu, sh.group);
         } else if (cmd == "state") {

@@ -328,6 +328,26 @@ def test_fused_replicas_must_fit(driver):
     assert got == [f"fuse {v}" for v in want.values()]
 
 
+def test_small_synchronous_shapes(driver):
+    """fp32 steps below 5M coordinates take shapes of their own; bf16 and
+    larger ones the table of large vectors, in which one and two learners, and 17
+    to 20 without momentum, have their own."""
+    for n in (500_000, 2_999_999, 3_000_000, 4_999_999):
+        cases = [(k, m) for k in range(1, 65) for m in (0, 1)]
+        out = run_driver(driver, [f"sync_shape {k} {m} 0 {n}" for (k, m) in cases])
+        for (k, m), line in zip(cases, out):
+            b, f, g = map(int, line.split()[1:])
+            assert 0 <= b <= 4 and f == 0 and g in (4, 8, 12, 16), (k, m, n)
+    edge = {(16, 0, 0, 4_999_999): (4, 0, 4), (16, 0, 0, 5_000_000): (1, 0, 16),
+            (16, 1, 0, 3_000_000): (3, 0, 4), (16, 0, 1, 1_000_000): (2, 0, 4),
+            (27, 0, 0, 2_999_999): (4, 0, 4), (28, 0, 0, 2_999_999): (2, 0, 4),
+            (28, 0, 0, 3_000_000): (1, 0, 16), (16, 0, 0, 499_999): (1, 0, 16),
+            (1, 0, 0, 17_000_000): (0, 0, 16), (2, 0, 0, 17_000_000): (4, 0, 16),
+            (17, 0, 0, 61_000_000): (2, 0, 4), (21, 0, 0, 61_000_000): (1, 0, 16)}
+    got = run_driver(driver, [f"sync_shape {k} {m} {b} {n}" for (k, m, b, n) in edge])
+    assert got == [f"sync_shape {x} {y} {z}" for (x, y, z) in edge.values()]
+
+
 def test_joining_rule(driver):
     """Which steps of a script go out in one launch: (steps, gradients and
     replicas a step, replicas that stay of all, bytes of a value, momentum,
