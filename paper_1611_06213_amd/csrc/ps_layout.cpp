@@ -45,26 +45,29 @@ int fronts_log2_for(const void *const *ptrs, int count) {
 
 namespace {
 
-// apply_shape below kMidVector coordinates. Measured at 100k, 1M and 4M for
-// the depths 1, 2, 4, 8, 16, 32 and 64; the depths between take a neighbour's.
+// apply_shape below kMidVector coordinates. Measured from 100k to 4.9M, from
+// server rows, separate allocations and rows of a packed tensor, for the depths 1
+// to 64; the figures are the most that a shape lost to the best one in its range.
 ApplyShape small_apply_shape(int k, bool momentum, bool bf16, size_t n) {
     const bool tiny = n < kTinyVector;
     if (bf16) {
         if (k <= 11 && !momentum) return {k <= 2 ? 4 : 3, 8};
-        if (k <= 23 || tiny) return {2, 16};
-        return {2, 4};
+        if (k <= 31 || tiny) return {2, 16};
+        // 32 and 40 gradients: up to 2.9M 5% ({2, 4} 10%), from there 7% (8%)
+        if (k <= 47) return n < 3000000 ? ApplyShape{2, 16} : ApplyShape{2, 4};
+        if (momentum) return n < 850000 ? ApplyShape{2, 16} : ApplyShape{2, 4};
+        return n < 2400000 ? ApplyShape{2, 4} : ApplyShape{1, 24};   // 6% ({2, 4} 8%)
     }
-    if (momentum) {
-        if (k <= 1) return {4, 16};
-        if (k <= 9) return {0, 16};
-        if (k <= 13) return {2, 12};
-        if (k <= 31) return {2, 16};
-        if (k <= 47 && !tiny) return {2, 4};
-        return {1, 32};
-    }
+    if (k <= 1 && momentum) return {4, 16};
     if (k <= 9) return {0, 16};
-    if (k <= 31) return {2, 16};
-    return {1, 32};
+    if (k <= 15) return {4, 16};
+    const bool few = n < 1500000;   // six rounds of blocks at one a unit
+    if (k <= 31) return few && !tiny ? ApplyShape{4, 16} : ApplyShape{2, 16};
+    if (tiny) return {1, 32};
+    if (n <= (1u << 19)) return {2, 4};   // one round of two blocks a unit
+    if (few) return momentum ? ApplyShape{4, 4} : ApplyShape{4, 8};   // 4% ({2, 4} 17%)
+    if (momentum) return {1, 32};                                     // 6% ({2, 4} 10%)
+    return k < 40 ? ApplyShape{2, 24} : ApplyShape{1, 8};             // 5%
 }
 
 // sync_shape below kMidVector coordinates, fp32 (the same kind of figures; the

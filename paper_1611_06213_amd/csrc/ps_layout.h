@@ -93,10 +93,9 @@ constexpr size_t kSmallVector = 20000000;
 // group at once (kernel time, from the table of large vectors to this one; 1M:
 // fp32 with momentum k = 4 7.8 -> 6.9 us, 16 16.1 -> 14.9; bf16 with momentum
 // k = 32 17.8 -> 15.0; bf16 k = 64 25.9 -> 22.8; 4M: fp32 with momentum k = 16
-// 54.8 -> 51.7, bf16 with momentum k = 64 98.8 -> 89.8). At 7M the two are
-// within 5% of each other either way. Below kTinyVector one round of blocks holds
-// everything, and all of a lane's loads go out together (100k, fp32 k = 64: 10.2
-// -> 8.4 us).
+// 54.8 -> 51.7). At 7M the two are within 5% of each other either way. Below
+// kTinyVector one round of blocks holds everything, and all of a lane's loads go
+// out together (100k, fp32 k = 64: 10.2 -> 8.4 us).
 // `widened`: the launch also writes more than one fp32 replica from bf16
 // gradients. Its 8-coordinate lanes write each in two stores 32 bytes apart, and
 // more than two blocks a unit then keep more half-written lines than L2 holds (no
