@@ -767,6 +767,19 @@ def test_sync_sizes_and_alignment(torch, n):
             _run_sync(torch, n, 16, 2, 0.9, gdt, offset=offset, seed=n + offset)
 
 
+@pytest.mark.parametrize("k", [1, 2, 5, 16, 28, 40])
+@pytest.mark.parametrize("n", [500_003, 1_500_001, 3_000_017])
+def test_launch_shapes_of_small_vectors(torch, n, k):
+    """The launch shapes between 0.5M and 5M coordinates, just above the sizes
+    where they change, from rows at element boundaries: applies with replicas
+    (fp32 ones of bf16 gradients too) and synchronous steps."""
+    for momentum in (0.0, 0.9):
+        for gdt, pdt in ((ps.PS_F32, ps.PS_F32), (ps.PS_BF16, ps.PS_F32)):
+            _run_edge(torch, n, k, momentum, gdt, pdt, offset_g=2 if gdt == ps.PS_BF16 else 1, offset_d=1,
+                      seed=k)
+        _run_sync(torch, n, k, 1, momentum, ps.PS_F32, offset=1, seed=k)
+
+
 def test_sync_rejects_mixed_dtypes(torch):
     n = 1000
     srv = ps.ParameterServer(n, 0.1, 0.0, queue_depth=4)
