@@ -65,9 +65,10 @@ ApplyShape small_apply_shape(int k, bool momentum, bool bf16, size_t n) {
     if (k <= 31) return few && !tiny ? ApplyShape{4, 16} : ApplyShape{2, 16};
     if (tiny) return {1, 32};
     if (n <= (1u << 19)) return {2, 4};   // one round of two blocks a unit
-    if (few) return momentum ? ApplyShape{4, 4} : ApplyShape{4, 8};   // 4% ({2, 4} 17%)
-    if (momentum) return {1, 32};                                     // 6% ({2, 4} 10%)
-    return k < 40 ? ApplyShape{2, 24} : ApplyShape{1, 8};             // 5%
+    if (n <= (1u << 20)) return {4, 4};   // one of four: 5% ({2, 4} 17%)
+    // 5% (at 1.1M and 1.2M {2, 4} 9%)
+    if (few || (k < 40 && n < 2000000)) return {2, 16};
+    return {1, 16};   // 8%, on average 1.4% ({1, 32} 8%, 3%)
 }
 
 // sync_shape below kMidVector coordinates, fp32 (the same kind of figures; the

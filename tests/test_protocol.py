@@ -328,6 +328,21 @@ def test_fused_replicas_must_fit(driver):
     assert got == [f"fuse {v}" for v in want.values()]
 
 
+def test_small_apply_shapes(driver):
+    """The sizes at which fp32 applies of 32 gradients and more, and bf16 ones of
+    24 and more, change their shape below 5M coordinates, and the depths."""
+    edge = {(32, 1, 0, 1 << 19): (2, 0, 4), (32, 1, 0, (1 << 19) + 1): (4, 0, 4),
+            (64, 0, 0, 1 << 20): (4, 0, 4), (64, 0, 0, (1 << 20) + 1): (2, 0, 16),
+            (40, 1, 0, 1_499_999): (2, 0, 16), (40, 1, 0, 1_500_000): (1, 0, 16),
+            (39, 0, 0, 1_999_999): (2, 0, 16), (39, 0, 0, 2_000_000): (1, 0, 16),
+            (31, 1, 0, 1_499_999): (4, 0, 16), (31, 1, 0, 1_500_000): (2, 0, 16),
+            (47, 0, 1, 2_999_999): (2, 0, 16), (47, 0, 1, 3_000_000): (2, 0, 4),
+            (48, 1, 1, 849_999): (2, 0, 16), (48, 1, 1, 850_000): (2, 0, 4),
+            (48, 0, 1, 2_399_999): (2, 0, 4), (48, 0, 1, 2_400_000): (1, 0, 24)}
+    got = run_driver(driver, [f"shape {k} {m} {b} {n}" for (k, m, b, n) in edge])
+    assert got == [f"shape {x} {y} {z}" for (x, y, z) in edge.values()]
+
+
 def test_small_synchronous_shapes(driver):
     """fp32 steps below 5M coordinates take shapes of their own; bf16 and
     larger ones the table of large vectors, in which one and two learners, and 17
