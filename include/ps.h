@@ -248,9 +248,10 @@ int ps_set_queue_mode(ps_server *ps, int mode, int slots_per_learner);
  * offsets within 2 MiB and their length -- four fronts for gradients of 500 MB
  * and more when at least 8 buffers take part and more than half of the
  * gradient, w and v buffers share one 4 KiB offset (as separately allocated,
- * 2 MiB-aligned buffers do), one front otherwise (ps_alloc_rows buffers). Results are identical either way; only the
- * order in which the grid visits coordinates changes. Holds for the joined
- * launches of a script (ps_run) as for single ones. */
+ * 2 MiB-aligned buffers do), one front otherwise (ps_alloc_rows buffers).
+ * Results are identical either way; only the order in which the grid visits
+ * coordinates changes. Holds for the joined launches of a script (ps_run) as
+ * for single ones. */
 int ps_set_fronts(ps_server *ps, int fronts_log2);
 
 /* Override the launch shape of the apply (Eq. "asgd") and synchronous-step
